@@ -68,7 +68,8 @@ METRIC = "rows/sec for SHAP values and SHAP interaction values; % FP32 VALU peak
 CSRC = os.path.join(ROOT, "paper_2010_13972_amd", "csrc")
 KERNEL_SOURCES = [os.path.join(CSRC, f) for f in (
     "gts_shap_kernel.h", "gts_launch.h", "gts_kernels.hip", "gts_shap_f32.hip",
-    "gts_shap_f64.hip", "gts_inter_f32.hip", "gts_inter_f64.hip", "gts_prune.hip")]
+    "gts_shap_f64.hip", "gts_inter_f32.hip", "gts_inter_f64.hip", "gts_inter_quad.h",
+    "gts_inter_quad_f32.hip", "gts_inter_quad_f64.hip", "gts_prune.hip")]
 
 WORKLOAD_TEXT = {
     "tiny": "tiny: 10 full depth-3 trees, M=8, X~U[0,1), 256 rows",

@@ -47,7 +47,7 @@ def _run(cmd, verbose):
 
 
 KERNEL_UNITS = ["gts_kernels", "gts_shap_f32", "gts_shap_f64", "gts_inter_f32", "gts_inter_f64",
-                "gts_prune"]
+                "gts_inter_quad_f32", "gts_inter_quad_f64", "gts_prune"]
 RESOURCES = os.path.join(BUILD, "kernel_resources.txt")
 
 

@@ -54,12 +54,58 @@ DeviceInfo device_info() {
 
 inline int odd_at_least(int n) { return n | 1; }
 
+// Interaction values of paths of 9 to 16 features: the quadrature kernel, on the
+// largest tile of 16, 8 or 4 rows a workgroup's LDS holds; false where none fits
+// (then the runtime-length code runs, as for longer paths).  Slices as for the
+// other interaction launches: at most one round of workgroups.
+template <typename T>
+bool plan_quad(const gts_model* m, int64_t rows, const DeviceInfo& dev, Plan& plan) {
+  const int q = m->max_path_len - 1;
+  if (q <= kMaxUnrolledInter || q > kMaxUnrolledQuad) return false;
+  const int M = m->num_features, G = m->num_groups;
+  auto lds = [&](int rw, int waves, bool wide) {
+    return sizeof(T) == 8 ? quad_lds_f64(M, rw, waves, true) : quad_lds_f32(M, rw, waves, wide);
+  };
+  struct Shape {
+    int rw, waves;
+    bool wide;   // tile in double (always for fp64 models)
+  };
+  constexpr Shape f32[] = {{16, 16, true}, {16, 16, false}, {8, 16, false}, {4, 8, false}};
+  constexpr Shape f64[] = {{16, 8, true}, {8, 8, true}, {4, 8, true}};
+  plan.RW = 0;
+  for (int i = 0; i < (sizeof(T) == 8 ? 3 : 4) && plan.RW == 0; ++i) {
+    const Shape& x = sizeof(T) == 8 ? f64[i] : f32[i];
+    if ((int64_t)lds(x.rw, x.waves, x.wide) + kQuadStaticLds > dev.lds_per_block) continue;
+    plan.RW = x.rw;
+    plan.waves = x.waves;
+    plan.wide_tile = x.wide;
+  }
+  if (plan.RW == 0) return false;
+  plan.quad = true;
+  plan.priv = false;
+  plan.lds = lds(plan.RW, plan.waves, plan.wide_tile);
+  plan.sx = odd_at_least(M);
+  plan.width = (M + 1) * (M + 1);
+  plan.tiles = (rows + plan.RW - 1) / plan.RW;
+  const int64_t base = plan.tiles * G;
+  const int64_t per_cu = std::max<int64_t>(
+      1, std::min<int64_t>(32 / plan.waves, dev.lds_per_cu / (int64_t)(plan.lds + kQuadStaticLds)));
+  const int64_t round = per_cu * dev.cus;
+  plan.splits = (int)std::max<int64_t>(
+      1, std::min<int64_t>(round / base, std::max<int64_t>(1, m->num_bins / G / plan.waves)));
+  plan.min_splits = plan.splits;
+  return true;
+}
+
 template <typename T, bool INTER>
 gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, Plan& plan) {
   const int M = m->num_features;
   const int G = m->num_groups;
   const int64_t width64 = INTER ? (int64_t)(M + 1) * (M + 1) : (int64_t)(M + 1);
   if (width64 > (1 << 30)) return fail(GTS_EINVAL, "M = %d is too large", M);
+  if constexpr (INTER) {
+    if (plan_quad<T>(m, rows, dev, plan)) return GTS_OK;
+  }
   const int32_t width = (int32_t)width64;
   const int32_t sx = odd_at_least(M);
   // interactions keep the upper triangle of each row's block in LDS
@@ -198,6 +244,8 @@ gts_status launch(const gts_model* m, const void* blob, const float* X, int64_t 
                : plan_launch<float, false>(m, rows, dev, plan);
   if (st != GTS_OK) return st;
   const KernelArgs a{m, blob, X, rows, ld, phi, stream};
+  if (plan.quad)
+    return m->dtype == GTS_F64 ? launch_inter_quad_f64(a, plan) : launch_inter_quad_f32(a, plan);
   if (m->dtype == GTS_F64) return inter ? launch_inter_f64(a, plan) : launch_shap_f64(a, plan);
   return inter ? launch_inter_f32(a, plan) : launch_shap_f32(a, plan);
 }

@@ -19,6 +19,11 @@ constexpr int kMaxUnrolledInter = 8;
 // fp32 G-form loses accuracy beyond 12), for either model dtype.
 constexpr int kMaxUnrolledShapF64 = 16;
 
+// Interaction values of paths of up to 16 features run by quadrature where the
+// model has longer ones than the unrolled code takes.
+constexpr int kMaxUnrolledQuad = 16;
+constexpr int64_t kQuadStaticLds = 512;   // that kernel's static LDS, rounded up
+
 // Kernel variant by the model's longest path: every path has at most 8
 // features, at most 12, at most 16 (SHAP values only), or any length up to a
 // full bin (63).
@@ -50,6 +55,8 @@ struct Plan {
   int64_t tiles = 0;
   int qmax = kQLong;
   size_t rank_off = 0;   // LDS offset of the rank tables (0: none)
+  bool quad = false;     // interactions by quadrature (gts_inter_quad.h)
+  bool wide_tile = false;   // that kernel's tile in double for an fp32 model
 };
 
 // Arguments of one gts_shap / gts_shap_interactions call.
@@ -69,5 +76,10 @@ gts_status launch_shap_f32(const KernelArgs& a, const Plan& p);
 gts_status launch_shap_f64(const KernelArgs& a, const Plan& p);
 gts_status launch_inter_f32(const KernelArgs& a, const Plan& p);
 gts_status launch_inter_f64(const KernelArgs& a, const Plan& p);
+gts_status launch_inter_quad_f32(const KernelArgs& a, const Plan& p);
+gts_status launch_inter_quad_f64(const KernelArgs& a, const Plan& p);
+// LDS of a workgroup of the quadrature kernel.
+size_t quad_lds_f32(int M, int rows, int waves, bool wide);
+size_t quad_lds_f64(int M, int rows, int waves, bool wide);
 
 }  // namespace gts

@@ -1,0 +1,77 @@
+"""Interaction values of models whose longest path holds 9 to 16 features (the
+quadrature kernel), against the oracle's conditioning route: chains at every
+path length around its padded variants, and one model per tile shape (16, 8 and
+4 rows, tiles in float and in double), with shorter paths, zero covers, ties,
+several groups, ragged rows, a pruned model and rows that are not finite."""
+import numpy as np
+import pytest
+
+from paper_2010_13972_amd import gts, synth
+from parity import assert_parity
+from test_gpu_shap import chain_tree
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    return torch
+
+
+def run(torch, model, X):
+    out = gts.shap_interactions(model, torch.from_numpy(np.ascontiguousarray(X)).cuda())
+    torch.cuda.synchronize()
+    return out.cpu().numpy().astype(np.float64)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("depth", [9, 10, 11, 13, 15, 16])
+def test_chains(torch, orc, depth, dtype):
+    """The chain's leaves give paths of every length from 1 to depth."""
+    rng = np.random.default_rng(depth)
+    ens = synth.ensemble_from_lists([chain_tree(depth, 16, rng), chain_tree(9, 16, rng)], M=16)
+    X = rng.random((19, 16)).astype(np.float32)
+    print("chain", depth, dtype, flush=True)
+    got = run(torch, gts.prepare(ens, dtype), X)
+    assert_parity(got, orc.interactions(ens, X), dtype, 2, what=f"chain {depth}")
+
+
+# (M, dtype, rows per tile of the launch)
+SHAPES = [(12, "f32", 16), (50, "f32", 16), (80, "f32", 8), (110, "f32", 4),
+          (20, "f64", 16), (50, "f64", 8), (75, "f64", 4)]
+
+
+@pytest.mark.parametrize("M,dtype,rw", SHAPES)
+def test_tile_shapes(torch, orc, M, dtype, rw):
+    w = synth.random_workload(900 + M, num_trees=9, max_depth=16, p_split=0.75, M=M, num_groups=3,
+                              n_bg=60, rows=37, max_leaves=200)
+    print("shape", M, dtype, rw, flush=True)
+    model = gts.prepare(w.ensemble, dtype)
+    assert 9 <= model.desc.max_path_len - 1 <= 16
+    assert gts.launch_config(model, 37, interactions=True)["rows_per_tile"] == rw
+    want = orc.interactions(w.ensemble, w.X)
+    assert_parity(run(torch, model, w.X), want, dtype, 2, what=f"M={M}")
+    X = torch.from_numpy(w.X).cuda()
+    pruned = gts.shap_interactions(gts.prune(model, X), X)
+    assert_parity(pruned.cpu().numpy().astype(np.float64), want, dtype, 2, what=f"pruned M={M}")
+
+
+def test_a_value_that_is_not_finite_is_in_no_range(torch):
+    """NaN and +inf fail every element's range test: a row of either gives what
+    the other gives, finite everywhere, and the rows beside it are unchanged."""
+    w = synth.random_workload(77, num_trees=6, max_depth=15, p_split=0.8, M=14, n_bg=60, rows=18,
+                              max_leaves=150)
+    model = gts.prepare(w.ensemble, "f64")
+    assert 9 <= model.desc.max_path_len - 1 <= 16
+    base = run(torch, model, w.X)
+    outs = []
+    for bad in (np.nan, np.inf):
+        X = w.X.copy()
+        X[5, 3] = bad
+        outs.append(run(torch, model, X))
+    assert np.isfinite(outs[0]).all()
+    np.testing.assert_allclose(outs[0], outs[1], rtol=0, atol=1e-12)
+    keep = np.arange(18) != 5
+    np.testing.assert_allclose(outs[0][keep], base[keep], rtol=0, atol=1e-12)
