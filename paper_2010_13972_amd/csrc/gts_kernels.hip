@@ -111,14 +111,17 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
   // interactions keep the upper triangle of each row's block in LDS
   const int32_t sp = odd_at_least(INTER ? (int32_t)((int64_t)(M + 1) * (M + 2) / 2) : width);
   // Row tile and accumulation.  If 64 rows with a private phi tile for each
-  // of 4 waves fit in half a CU's LDS (two workgroups per CU), use them (no
-  // contention, no atomics).  Otherwise 8 waves share one tile: the largest
-  // RW whose tiles fit in 64 KB (several workgroups per CU), or, if that
-  // would leave fewer than 8 rows per wave, 8 rows (then 4) using up to the
-  // whole LDS of a workgroup.
+  // of 4 waves fit in 64 KB of LDS, use them (no contention, no atomics).
+  // Otherwise 8 waves share one tile (12 for SHAP values of short paths on 64
+  // rows, whose 64 registers leave room for 24 waves a CU): the largest RW whose
+  // tiles fit in 64 KB (SHAP values, in double: 80 KB, two workgroups per CU),
+  // or, if that would leave fewer than 8 rows per wave, 8 rows (then 4) using up
+  // to the whole LDS of a workgroup.
   auto need = [&](int rw, int waves, bool priv) {
+    // shared tiles of SHAP values hold doubles (TileT)
+    const size_t entry = INTER || priv || (rw == 4 && waves == 8) ? sizeof(T) : sizeof(double);
     const size_t tiles = (size_t)rw * ((size_t)sx * sizeof(float) +
-                                       (priv ? (size_t)waves : 1) * (size_t)sp * sizeof(T));
+                                       (priv ? (size_t)waves : 1) * (size_t)sp * entry);
     const size_t stage = rw == 64 ? sizeof(Stage<T, false>) : sizeof(Stage<T, true>);
     return ((tiles + 15) & ~(size_t)15) + (size_t)waves * stage;
   };
@@ -126,14 +129,18 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
   int waves = 8;
   bool priv = false;
   constexpr int64_t kSmallTile = 64 * 1024;  // leaves room for several workgroups per CU
+  constexpr int64_t kHalfCu = 80 * 1024;     // two workgroups per CU
   if ((int64_t)need(64, 4, true) <= std::min<int64_t>(kSmallTile, dev.lds_per_block)) {
     RW = 64;
     waves = 4;
     priv = true;
   } else {
     for (int cand : {64, 32, 16, 8}) {
-      if ((int64_t)need(cand, 8, false) <= std::min<int64_t>(kSmallTile, dev.lds_per_block)) {
+      const int w = cand == 64 && !INTER && m->max_path_len - 1 <= kQShort ? 12 : 8;
+      const int64_t budget = INTER ? kSmallTile : kHalfCu;
+      if ((int64_t)need(cand, w, false) <= std::min<int64_t>(budget, dev.lds_per_block)) {
         RW = cand;
+        waves = w;
         break;
       }
     }
@@ -158,6 +165,10 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
       const int cap = 24;
       int best = 0;
       for (int w : {8, 12, 16}) {
+        // 16 waves leave 128 registers, and fp64 paths of 13-16 features spill
+        // much of a path's state there: 0.39 against 0.22 ms at 12 waves (M = 635,
+        // 886 rows), 1.46 against 0.56 (M = 300, 2000 rows)
+        if (w == 16 && sizeof(T) == 8 && m->max_path_len - 1 > kQMid) continue;
         const int64_t n = need(RW, w, false);
         if (n > dev.lds_per_block) continue;
         const int per_cu = (int)std::min<int64_t>(cap, w * (dev.lds_per_cu / n));

@@ -15,8 +15,8 @@ namespace gts {
 // per-lane private memory; only the long-path kernel variants contain it.
 constexpr int kMaxUnrolledShap = 12;
 constexpr int kMaxUnrolledInter = 8;
-// SHAP paths of 13-16 features run unrolled code in fp64 arithmetic (the
-// fp32 G-form loses accuracy beyond 12), for either model dtype.
+// SHAP paths of 13-16 features run unrolled code in a variant of their own, since
+// they need more registers.
 constexpr int kMaxUnrolledShapF64 = 16;
 
 // Interaction values of paths of up to 16 features run by quadrature where the

@@ -19,7 +19,7 @@
 // for interactions), so a wave never diverges on path length.  This does the
 // q^2 work of a path once per row instead of spreading it over q lanes that
 // then need q shuffles each.  Each kernel is built for the model's longest
-// path: up to 8 features, up to 12, up to 16 (fp64 arithmetic), or longer;
+// path: up to 8 features, up to 12, up to 16, or longer;
 // only the last holds the runtime-loop code for long paths and its per-lane
 // private arrays.
 //
@@ -33,26 +33,28 @@
 // the tile's row keys; otherwise it tests each path's elements in turn.  The
 // multi-path rounds (RW < 64) compute every pair.
 //
-// Arithmetic.  EXTEND keeps permutation weights w_k, which are the
-// coefficients E_k of prod_k (z_k + o_k t) scaled by k!(l-k)!/(l+1)!.  The
+// Arithmetic, SHAP values.  The Shapley weights are Beta integrals, so a path's
+// values are integrals of products of its elements' factors, and a Gauss-Legendre
+// rule of ceil(q / 2) nodes gives them exactly (shap_math): 2 q^2 multiply-adds per
+// (row, path), no selects, no divisions, no cancellation.
+//
+// Arithmetic, interaction values.  EXTEND keeps permutation weights w_k, which are
+// the coefficients E_k of prod_k (z_k + o_k t) scaled by k!(l-k)!/(l+1)!.  The
 // kernels keep E_k: adding an element is E_k <- z E_k + o E_{k-1} (one
 // multiply-add), and the scale factors reappear in the final sums as the
 // Shapley weights c_k = k!(q-1-k)!/q!.  UNWIND of an element with o = 1
 // divides the polynomial by (z + t) from the top coefficient down, like
-// Algorithm 1's o != 0 branch.  Its Shapley-weighted sum is linear in the
-// quotient, so it is a polynomial in -z whose coefficients
-// G_m = sum_{j>m} c_{j-1-m} E_j are shared by every element of the path: one
-// multiply-add per coefficient per element (Horner) instead of a division and
-// a weighted sum.  For o = 0 the contribution reduces to -v * sum_k c_k E_k,
-// shared by every such element, so no division by a zero fraction is ever
-// needed.  Per-element constants of a path (v (1 - z)) are computed once per
-// bin when it is staged, not once per row.
+// Algorithm 1's o != 0 branch; for o = 0 the contribution reduces to
+// -v * sum_k c_k E_k, shared by every such element, so no division by a zero
+// fraction is ever needed.  v (1 - z) is computed once per bin when it is staged,
+// not once per row.
 //
 // Accumulation.  A workgroup owns a tile of RW rows of one output group and a
-// slice of that group's bins.  Contributions go to a phi tile in LDS (an
-// atomic add built from compare-and-swap, the compare-and-swaps of a path
-// issued together so their LDS round trips overlap) or, when a wave has a
-// tile of its own and one path at a time, a plain read-modify-write.  An
+// slice of that group's bins.  Contributions go to a phi tile in LDS: for SHAP
+// values a tile of doubles, which gfx950 adds to natively; for interaction values
+// an atomic add built from compare-and-swap, those of a path issued together so
+// their LDS round trips overlap; or, when a wave has a tile of its own and one
+// path at a time, a plain read-modify-write.  An
 // interaction pair is added to one of its two entries and the tile write sums
 // the mirror entries, so the output is exactly symmetric.  The tile is written
 // to HBM once (atomically added when several workgroups share the row tile).
@@ -165,11 +167,12 @@ __host__ __device__ constexpr double shapley_weight(int n, int k) {
   return 1.0 / ((double)n * c);
 }
 
-// Add to a phi-tile entry in LDS.  A compare-and-swap loop on the bit
-// pattern: gfx950 executes the LDS float add atomic (ds_add_f32) one lane at
-// a time, about 190 cycles per wave64 instruction, while the integer
-// compare-and-swap runs at the rate of a plain read-modify-write; without a
-// conflict the loop runs once.
+// Add to a phi-tile entry in LDS.  Measured per wave64 instruction and CU (16
+// waves, conflict-free): ds_add_f64 8 cycles and no result to wait for; ds_add_f32
+// 192 cycles, one lane at a time; a compare-and-swap on a float's bit pattern 14
+// cycles and a round trip of 200 (without a conflict the loop runs once).  So a
+// shared tile of SHAP values holds doubles for either dtype (TileT), and the
+// compare-and-swap remains for the tiles that only fit in float.
 __device__ __forceinline__ void lds_add(float* p, float v) {
   unsigned* q = reinterpret_cast<unsigned*>(p);
   unsigned old = *q, assumed;
@@ -179,13 +182,7 @@ __device__ __forceinline__ void lds_add(float* p, float v) {
   } while (old != assumed);
 }
 __device__ __forceinline__ void lds_add(double* p, double v) {
-  unsigned long long* q = reinterpret_cast<unsigned long long*>(p);
-  unsigned long long old = *q, assumed;
-  do {
-    assumed = old;
-    old = atomicCAS(q, assumed,
-                    (unsigned long long)__double_as_longlong(__longlong_as_double((long long)assumed) + v));
-  } while (old != assumed);
+  __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // Bit patterns of the tile entries, for compare-and-swap.
@@ -200,6 +197,13 @@ template <> struct Bits<double> {
   static __device__ __forceinline__ U of(double x) { return (U)__double_as_longlong(x); }
   static __device__ __forceinline__ double val(U u) { return __longlong_as_double((long long)u); }
 };
+
+// The type of the phi tile's entries: double for the shared tiles of SHAP values,
+// except 4 rows at 8 waves, the shape for phi rows too wide for a tile of doubles;
+// the model's type for private tiles (no atomics) and interaction values (the
+// tile's size decides the rows per workgroup there).
+template <typename T, int RW, bool INTER, int WAVES, bool PRIV>
+using TileT = std::conditional_t<!INTER && !PRIV && !(RW == 4 && WAVES == 8), double, T>;
 
 // How a lane adds the contributions of one path to the phi tile.
 //   kExclusive  no other lane or wave updates these entries meanwhile (a
@@ -218,8 +222,8 @@ enum AddMode { kExclusive, kBatched, kPaired };
 
 // Add val[i] to *p[i] for every i with on[i]; the addresses of one lane are
 // distinct.  p[i] must be a valid tile address even where on[i] is false.
-template <AddMode MODE, typename T, int N>
-__device__ __forceinline__ void tile_add(T* const (&p)[N], const T (&val)[N], const bool (&on)[N]) {
+template <AddMode MODE, typename T, typename V, int N>
+__device__ __forceinline__ void tile_add(T* const (&p)[N], const V (&val)[N], const bool (&on)[N]) {
   if constexpr (MODE == kExclusive) {
     T old[N];
 #pragma unroll
@@ -227,6 +231,11 @@ __device__ __forceinline__ void tile_add(T* const (&p)[N], const T (&val)[N], co
 #pragma unroll
     for (int i = 0; i < N; ++i)
       if (on[i]) *p[i] = old[i] + val[i];
+  } else if constexpr (sizeof(T) == 8) {
+    // native and without a result to wait for
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (on[i]) lds_add(p[i], (T)val[i]);
   } else {
     using U = typename Bits<T>::U;
     U old[N], got[N];
@@ -416,11 +425,11 @@ __device__ __forceinline__ int path_q(int info) { return (info >> 8) & 0xff; }
 __device__ __forceinline__ int path_n0(int info) { return info >> 16; }
 
 // Feature, presence test o_k = [lower <= x < upper] (on keys), zero fraction and
-// v (1 - z) of the first Q feature elements of the path whose root is in
+// (interaction values) v (1 - z) of the first Q feature elements of the path whose root is in
 // slot s (wave-uniform when UNIFORM).  A lane whose path has q < Q features
 // reads the neutral element for k >= q; on[k] = k < q marks the elements
 // whose contributions are written.
-template <typename T, int Q, bool UNIFORM, bool GAPPED>
+template <typename T, int Q, bool UNIFORM, bool INTER, bool GAPPED>
 __device__ __forceinline__ void load_path(const Stage<T, GAPPED>* st, int s, int q,
                                           const int* __restrict__ xrow, int (&f)[Q],
                                           bool (&o)[Q], T (&z)[Q], T (&w)[Q], bool (&on)[Q]) {
@@ -429,11 +438,12 @@ __device__ __forceinline__ void load_path(const Stage<T, GAPPED>* st, int s, int
     const bool real = UNIFORM || k < q;
     const int e = real ? s + 1 + k : Stage<T, GAPPED>::kSlots;
     const int4 head = st->head[e];
-    f[k] = head.x;
-    o[k] = in_range(xrow[head.x], head.y, (unsigned)head.z);
+    // one path per wave: the feature in a scalar register
+    f[k] = UNIFORM && !INTER ? __builtin_amdgcn_readfirstlane(head.x) : head.x;
+    o[k] = in_range(xrow[f[k]], head.y, (unsigned)head.z);
     if constexpr (sizeof(T) == 4) z[k] = __int_as_float(head.w);
     else z[k] = st->aux[e].z;
-    w[k] = st->w(e);
+    if constexpr (INTER) w[k] = st->w(e);
     on[k] = real;
   }
 }
@@ -467,45 +477,97 @@ __device__ __forceinline__ void unwind_one(const T (&E)[Q + 1], T zi, T (&D)[Q])
 // per-lane path arithmetic
 // ---------------------------------------------------------------------------
 
-// SHAP values.  With D^i = E / (z_i + t) (synthetic division from the top,
-// D^i_k = sum_{j>k} E_j (-z_i)^{j-1-k}), the unwound sum of element i is
-// sum_k c_k D^i_k = sum_m (-z_i)^m G_m with G_m = sum_{j>m} c_{j-1-m} E_j.
-// phi[f_i] += v (1 - z_i) * that sum when o_i = 1, and -v sum_k c_k E_k
-// when o_i = 0.
-// C: the arithmetic's type (T, or double for paths of 13-16 features).
-template <typename T, int Q, AddMode MODE, typename C = T>
+// Gauss-Legendre nodes and weights on [0, 1], row N - 1 for N = 1..8 nodes.
+constexpr double kGaussNode[8][8] = {
+    {0.5},
+    {0.21132486540518711775, 0.78867513459481288223},
+    {0.11270166537925831149, 0.5, 0.88729833462074168848},
+    {0.0694318442029737124, 0.3300094782075718676, 0.6699905217924281324,
+     0.93056815579702628757},
+    {0.04691007703066800362, 0.23076534494715845449, 0.5, 0.76923465505284154551,
+     0.95308992296933199638},
+    {0.03376524289842398608, 0.16939530676686774318, 0.38069040695840154569,
+     0.61930959304159845431, 0.83060469323313225682, 0.96623475710157601392},
+    {0.02544604382862073776, 0.12923440720030278007, 0.29707742431130141654, 0.5,
+     0.70292257568869858346, 0.87076559279969721996, 0.97455395617137926222},
+    {0.01985507175123188417, 0.10166676129318663022, 0.23723379504183550708,
+     0.40828267875217509752, 0.59171732124782490245, 0.76276620495816449292,
+     0.89833323870681336978, 0.98014492824876811583}};
+constexpr double kGaussWeight[8][8] = {
+    {1},
+    {0.5, 0.5},
+    {0.27777777777777777778, 0.44444444444444444444, 0.27777777777777777778},
+    {0.17392742256872692872, 0.32607257743127307135, 0.32607257743127307135,
+     0.17392742256872692872},
+    {0.11846344252809454385, 0.23931433524968323406, 0.28444444444444444444,
+     0.23931433524968323406, 0.11846344252809454385},
+    {0.08566224618958517245, 0.18038078652406930377, 0.23395696728634552369,
+     0.23395696728634552369, 0.18038078652406930377, 0.08566224618958517245},
+    {0.0647424830844348467, 0.13985269574463833395, 0.19091502525255947241,
+     0.20897959183673469387, 0.19091502525255947241, 0.13985269574463833395,
+     0.0647424830844348467},
+    {0.05061426814518812961, 0.11119051722668723529, 0.15685332293894364364,
+     0.18134189168918099147, 0.18134189168918099147, 0.15685332293894364364,
+     0.11119051722668723529, 0.05061426814518812961}};
+
+// (1 - t)^n
+constexpr double pow_n(double x, int n) {
+  double r = 1.0;
+  for (int i = 0; i < n; ++i) r *= x;
+  return r;
+}
+
+// SHAP values.  The Shapley weights k! (q-1-k)! / q! are Beta integrals, so
+//   phi_i = v (o_i - z_i) integral over [0, 1] of
+//                         prod_{k != i} (z_k (1 - t) + o_k t) dt,
+// a polynomial of degree q - 1 that ceil(q / 2) Gauss-Legendre nodes integrate
+// exactly.  With tau = t / (1 - t) a node's factors are (1 - t)(z_k + o_k tau), one
+// multiply-add each from o_k in {0, 1}; the powers of 1 - t go into the node's
+// weight.  Products before and after each element give all the products of the
+// others: about 4 q operations a node, 2 q^2 in all, without selects, divisions or
+// cancellation: no factor is negative.  VALU issue bounds the launches.  Against
+// unwinding the path polynomial (with compare-and-swap adds): 100 trees of depth 8
+// over 54 features, 10 000 rows, 289 M to 205 M vector instructions and 0.38 to
+// 0.32 ms, error against float64 1.15e-7 to 0.8e-7; depth 16 (paths of up to 16
+// features, which needed fp64 arithmetic before) 2.17 to 0.91 ms, 2.1e-7 to 1.2e-7.
+template <typename T, int Q, AddMode MODE, typename A>
 __device__ __forceinline__ void shap_math(const int (&f)[Q], const bool (&o)[Q], const T (&z)[Q],
-                                          const T (&w)[Q], const bool (&on)[Q], T v,
-                                          T* __restrict__ prow) {
-  C zc[Q];
+                                          const bool (&on)[Q], T v, A* __restrict__ prow) {
+    constexpr int N = (Q + 1) / 2;
+  T of[Q], S[Q];
 #pragma unroll
-  for (int k = 0; k < Q; ++k) zc[k] = C(z[k]);
-  C E[Q + 1];
-  extend_all<C, Q>(o, zc, E);
-  C t_all = C(0);
-#pragma unroll
-  for (int k = 0; k < Q; ++k) t_all = fma(C(shapley_weight(Q, k)), E[k], t_all);
-  C G[Q];
-#pragma unroll
-  for (int m = 0; m < Q; ++m) {
-    G[m] = C(shapley_weight(Q, Q - 1 - m)) * E[Q];
-#pragma unroll
-    for (int j = Q - 1; j > m; --j) G[m] = fma(C(shapley_weight(Q, j - 1 - m)), E[j], G[m]);
+  for (int k = 0; k < Q; ++k) {
+    of[k] = o[k] ? T(1) : T(0);
+    S[k] = T(0);
   }
-  const C neg_vt = -C(v) * t_all;
-  T* p[Q];
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    constexpr const double(&t)[8] = kGaussNode[N - 1];
+    const T tau = T(t[n] / (1.0 - t[n]));
+    const T weight = v * T(kGaussWeight[N - 1][n] * pow_n(1.0 - t[n], Q - 1));
+    T a[Q], after[Q];
+#pragma unroll
+    for (int k = 0; k < Q; ++k) a[k] = fma(of[k], tau, z[k]);
+    after[Q - 1] = T(1);
+#pragma unroll
+    for (int k = Q - 2; k >= 0; --k) after[k] = k == Q - 2 ? a[k + 1] : a[k + 1] * after[k + 1];
+    T before = weight;
+#pragma unroll
+    for (int k = 0; k < Q; ++k) {
+      S[k] = k == Q - 1 ? S[k] + before : fma(before, after[k], S[k]);
+      before *= a[k];
+    }
+    // node by node: interleaved, they hold more registers than the occupancy
+    // allows
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  A* p[Q];
   T val[Q];
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
-    C s = G[Q - 1];
-#pragma unroll
-    for (int m = Q - 2; m >= 0; --m) s = fma(-zc[i], s, G[m]);
-    C a = C(w[i]) * s;
-    // several paths per wave: the lanes rarely agree on o_i, so a branch
-    // around the Horner evaluation only adds its cost (one path per wave:
-    // whole waves often have o_i = 0 and skip it)
-    if constexpr (MODE == kPaired) keep(a);
-    val[i] = T(o[i] ? a : neg_vt);
+    val[i] = (of[i] - z[i]) * S[i];
+    // not sunk into a branch around the add
+    if constexpr (MODE == kPaired) keep(val[i]);
     p[i] = prow + f[i];
   }
   tile_add<MODE>(p, val, on);
@@ -618,9 +680,9 @@ __device__ __forceinline__ void inter_math(const int (&f)[Q], const bool (&o)[Q]
 // features, in fp64 it stays far inside it for the longest path a wave64
 // holds (63 features).  FP64 FMAs run at the rate of unpacked FP32 ones on
 // gfx950.  q = 0 (no path) does nothing.
-template <typename T, bool INTER, AddMode MODE, bool GAPPED>
+template <typename T, typename A, bool INTER, AddMode MODE, bool GAPPED>
 __device__ void path_dyn(const Stage<T, GAPPED>* st, int s, int q, const int* __restrict__ xrow,
-                         T* __restrict__ prow, int stride) {
+                         A* __restrict__ prow, int stride) {
   double E[kMaxPathLen];
   double z[kMaxPathLen];
   double D[kMaxPathLen];
@@ -651,7 +713,7 @@ __device__ void path_dyn(const Stage<T, GAPPED>* st, int s, int q, const int* __
       for (int k = 0; k < q; ++k) s = fma(shapley_weight(q, k), D[k], s);
       const bool oi = (obits >> i) & 1u;
       const double phi = oi ? v * (1.0 - z[i]) * s : -v * t_all;
-      acc_add<MODE == kExclusive>(&prow[f[i]], (T)phi);
+      acc_add<MODE == kExclusive>(&prow[f[i]], (A)phi);
     }
   } else {
     double DD[kMaxPathLen];
@@ -682,41 +744,39 @@ __device__ void path_dyn(const Stage<T, GAPPED>* st, int s, int q, const int* __
         else delta = half_v * t_pair;
         diag[c] -= delta;
         diag[i] -= delta;
-        acc_add<MODE == kExclusive>(&prow[tri_at(f[i], f[c], stride)], (T)delta);
+        acc_add<MODE == kExclusive>(&prow[tri_at(f[i], f[c], stride)], (A)delta);
       }
     }
     for (int c = 0; c < q; ++c)
-      acc_add<MODE == kExclusive>(&prow[tri_row(f[c], stride) + f[c]], (T)diag[c]);
+      acc_add<MODE == kExclusive>(&prow[tri_row(f[c], stride) + f[c]], (A)diag[c]);
   }
 }
 
-template <typename T, int Q, bool UNIFORM, bool INTER, AddMode MODE, bool GAPPED, typename C = T>
+template <typename T, typename A, int Q, bool UNIFORM, bool INTER, AddMode MODE, bool GAPPED>
 __device__ __forceinline__ void path_fixed(const Stage<T, GAPPED>* st, int s, int q,
-                                           const int* __restrict__ xrow, T* __restrict__ prow,
+                                           const int* __restrict__ xrow, A* __restrict__ prow,
                                            int stride) {
   int f[Q];
   bool o[Q], on[Q];
   T z[Q], w[Q];
-  load_path<T, Q, UNIFORM, GAPPED>(st, s, q, xrow, f, o, z, w, on);
+  load_path<T, Q, UNIFORM, INTER, GAPPED>(st, s, q, xrow, f, o, z, w, on);
   const T v = st->w(s);
   if constexpr (INTER) inter_math<T, Q, MODE>(f, o, z, w, on, v, prow, stride);
-  else shap_math<T, Q, MODE, C>(f, o, z, w, on, v, prow);
+  else shap_math<T, Q, MODE>(f, o, z, on, v, prow);
 }
 
 // Q = features of the longest path in the wave's current set (uniform); q =
 // this lane's path (0: none).  QMAX = the kernel variant's longest path: the
 // runtime-length code exists only in the kQLong variants.
-template <typename T, bool UNIFORM, bool INTER, AddMode MODE, bool GAPPED, int QMAX>
+template <typename T, typename A, bool UNIFORM, bool INTER, AddMode MODE, bool GAPPED, int QMAX>
 __device__ __forceinline__ void dispatch(int Q, const Stage<T, GAPPED>* st, int s, int q,
-                                         const int* xrow, T* prow, int stride) {
+                                         const int* xrow, A* prow, int stride) {
   static_assert(kMaxUnrolledShap == 12 && kMaxUnrolledShapF64 == 16 && kMaxUnrolledInter == 8,
                 "update the case lists");
   static_assert(QMAX == kQShort || QMAX == kQMid || QMAX == kQExt || QMAX == kQLong,
                 "unknown variant");
 #define GTS_CASE(n) \
-  case n: path_fixed<T, n, UNIFORM, INTER, MODE, GAPPED>(st, s, q, xrow, prow, stride); break;
-#define GTS_CASE64(n) \
-  case n: path_fixed<T, n, UNIFORM, false, MODE, GAPPED, double>(st, s, q, xrow, prow, stride); break;
+  case n: path_fixed<T, A, n, UNIFORM, INTER, MODE, GAPPED>(st, s, q, xrow, prow, stride); break;
   switch (Q) {
     GTS_CASE(1) GTS_CASE(2) GTS_CASE(3) GTS_CASE(4) GTS_CASE(5) GTS_CASE(6)
     GTS_CASE(7) GTS_CASE(8)
@@ -727,22 +787,21 @@ __device__ __forceinline__ void dispatch(int Q, const Stage<T, GAPPED>* st, int 
           default:
             if constexpr (QMAX >= kQExt) {
               switch (Q) {
-                GTS_CASE64(13) GTS_CASE64(14) GTS_CASE64(15) GTS_CASE64(16)
+                GTS_CASE(13) GTS_CASE(14) GTS_CASE(15) GTS_CASE(16)
                 default:
                   if constexpr (QMAX == kQLong)
-                    path_dyn<T, false, MODE, GAPPED>(st, s, q, xrow, prow, stride);
+                    path_dyn<T, A, false, MODE, GAPPED>(st, s, q, xrow, prow, stride);
                   break;
               }
             }
             break;
         }
       } else if constexpr (QMAX == kQLong) {
-        path_dyn<T, INTER, MODE, GAPPED>(st, s, q, xrow, prow, stride);
+        path_dyn<T, A, INTER, MODE, GAPPED>(st, s, q, xrow, prow, stride);
       }
       break;
   }
 #undef GTS_CASE
-#undef GTS_CASE64
 }
 
 // Largest value of v over the wave (v in [0, 64)), from six ballots.
@@ -884,9 +943,9 @@ __device__ __forceinline__ uint64_t live_roots(const Bin<T>& b, int lane, uint64
 // the dead paths of a bin first and leaving them out of the rounds was
 // measured slower: a round is saved only when the live paths fit in fewer
 // rounds, and the test of every path costs more than that saves.)
-template <typename T, int RW, bool INTER, bool EXCL, int QMAX>
+template <typename T, typename A, int RW, bool INTER, bool EXCL, int QMAX>
 __device__ __forceinline__ void process_bin(Stage<T, RW < 64>* st, const Bin<T>& b, int lane,
-                                            const int* xrow, T* prow, int stride, bool sorted,
+                                            const int* xrow, A* prow, int stride, bool sorted,
                                             bool ranked, RankTables rt) {
   const BinIndex ix = index_bin(b, lane);
   const uint64_t roots = ix.roots;
@@ -909,7 +968,7 @@ __device__ __forceinline__ void process_bin(Stage<T, RW < 64>* st, const Bin<T>&
       const int q = word & 0xff;
       const int n0 = word >> 8;
       if (ranked || (q > 0 && (n0 == 0 || wave_live(b, rl, n0, xrow))))
-        dispatch<T, true, INTER, EXCL ? kExclusive : kBatched, false, QMAX>(q, st, rl, q, xrow,
+        dispatch<T, A, true, INTER, EXCL ? kExclusive : kBatched, false, QMAX>(q, st, rl, q, xrow,
                                                                              prow, stride);
     }
   } else {
@@ -926,7 +985,7 @@ __device__ __forceinline__ void process_bin(Stage<T, RW < 64>* st, const Bin<T>&
       const int qmax = sorted ? path_q(__builtin_amdgcn_readfirstlane(st->path[base]))
                               : wave_max_small(my_q);
       if (qmax > 0)
-        dispatch<T, false, INTER, kPaired, true, QMAX>(qmax, st, my_s, my_q, xrow, prow, stride);
+        dispatch<T, A, false, INTER, kPaired, true, QMAX>(qmax, st, my_s, my_q, xrow, prow, stride);
     }
   }
   // the next bin overwrites the stage
@@ -944,9 +1003,10 @@ __device__ __forceinline__ void process_bin(Stage<T, RW < 64>* st, const Bin<T>&
 // unit's row tiles together.  Either way each XCD's L2 holds about one
 // unit's bins at a time.
 template <typename T, int RW, bool INTER, int WAVES, bool PRIV, int QMAX>
-__global__ __launch_bounds__(64 * WAVES) void shap_kernel(DevModel<T> d, const float* __restrict__ X,
-                                                         T* __restrict__ phi, Launch L) {
+__global__ __launch_bounds__(64 * WAVES) void shap_kernel(
+    DevModel<T> d, const float* __restrict__ X, T* __restrict__ phi, Launch L) {
   extern __shared__ __align__(16) unsigned char smem[];
+  using A = TileT<T, RW, INTER, WAVES, PRIV>;
   constexpr int kThreads = 64 * WAVES;
   const int M = d.M;
   const int G = d.G;
@@ -977,12 +1037,13 @@ __global__ __launch_bounds__(64 * WAVES) void shap_kernel(DevModel<T> d, const f
     if (s >= b_step) return;   // the whole workgroup, before any barrier
   }
 
-  int* xs = reinterpret_cast<int*>(smem);   // the X tile, as fkey of each value
-  T* ps = reinterpret_cast<T*>(smem + (size_t)RW * L.sx * sizeof(float));
+  // the phi tile, then the X tile (as fkey of each value)
+  A* ps = reinterpret_cast<A*>(smem);
   constexpr int NT = PRIV ? WAVES : 1;  // phi tiles
   const int tile_elems = RW * L.sp;
+  int* xs = reinterpret_cast<int*>(smem + (size_t)NT * tile_elems * sizeof(A));
   Stage<T, RW < 64>* stages = reinterpret_cast<Stage<T, RW < 64>*>(
-      smem + (((size_t)RW * L.sx * sizeof(float) + (size_t)NT * tile_elems * sizeof(T) + 15) & ~(size_t)15));
+      smem + (((size_t)RW * L.sx * sizeof(float) + (size_t)NT * tile_elems * sizeof(A) + 15) & ~(size_t)15));
 
   // stage the X tile (coalesced along each row) and clear the phi tile
   for (int i = threadIdx.x; i < RW * M; i += kThreads) {
@@ -990,7 +1051,7 @@ __global__ __launch_bounds__(64 * WAVES) void shap_kernel(DevModel<T> d, const f
     const int64_t row = r0 + r;
     xs[r * L.sx + c] = fkey(row < L.rows ? X[row * L.ld + c] : 0.0f);
   }
-  for (int i = threadIdx.x; i < NT * tile_elems; i += kThreads) ps[i] = T(0);
+  for (int i = threadIdx.x; i < NT * tile_elems; i += kThreads) ps[i] = A(0);
   __syncthreads();
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1010,19 +1071,23 @@ __global__ __launch_bounds__(64 * WAVES) void shap_kernel(DevModel<T> d, const f
   // strided, every slice gets bins of every size.
   const int b_lo = gb0 + s;
   const int* xrow = xs + r * L.sx;
-  T* prow = ps + (PRIV ? wave * tile_elems : 0) + r * L.sp;
+  A* prow = ps + (PRIV ? wave * tile_elems : 0) + r * L.sp;
   const int stride = M + 1;
 
   int bi = b_lo + wave * b_step;
   if (bi < gb1) {
+    // the next bin is loaded while this one is computed; in 64-row shared tiles,
+    // whose many waves hide the load, its registers are worth more
+    constexpr bool kPrefetch = RW < 64 || PRIV;
     Bin<T> cur = load_bin(d, bi, lane);
     for (; bi < gb1; bi += WAVES * b_step) {
       Bin<T> nxt;
       const int bn = bi + WAVES * b_step;
-      if (bn < gb1) nxt = load_bin(d, bn, lane);
-      process_bin<T, RW, INTER, PRIV && RW == 64, QMAX>(stages + wave, cur, lane, xrow, prow,
-                                                        stride, L.sorted != 0, ranked, rt);
-      cur = nxt;
+      if (kPrefetch && bn < gb1) nxt = load_bin(d, bn, lane);
+      process_bin<T, A, RW, INTER, PRIV && RW == 64, QMAX>(stages + wave, cur, lane, xrow, prow,
+                                                           stride, L.sorted != 0, ranked, rt);
+      if (kPrefetch) cur = nxt;
+      else if (bn < gb1) cur = load_bin(d, bn, lane);
     }
   }
   __syncthreads();
@@ -1041,9 +1106,10 @@ __global__ __launch_bounds__(64 * WAVES) void shap_kernel(DevModel<T> d, const f
       const int a = c / stride;
       t = tri_at(a, c - a * stride, stride);
     }
-    T val = ps[rr * L.sp + t];
+    A sum = ps[rr * L.sp + t];
 #pragma unroll
-    for (int w = 1; w < NT; ++w) val += ps[w * tile_elems + rr * L.sp + t];
+    for (int w = 1; w < NT; ++w) sum += ps[w * tile_elems + rr * L.sp + t];
+    T val = (T)sum;
     if (c == W - 1 && s == 0) val += bias;
     T* out = phi + (row * G + g) * (int64_t)W + c;
     if (L.accumulate) unsafeAtomicAdd(out, val);
@@ -1107,7 +1173,7 @@ gts_status launch_shape(const KernelArgs& a, const Plan& p) {
   if (p.priv) return launch_rw<T, 64, INTER, 4, true, QMAX>(a, p);
 #define GTS_LAUNCH(rw, w) return launch_rw<T, rw, INTER, w, false, QMAX>(a, p)
   switch (p.RW) {
-    case 64: GTS_LAUNCH(64, 8);
+    case 64: GTS_LAUNCH(64, (INTER || QMAX > kQShort ? 8 : 12));
     case 32: GTS_LAUNCH(32, 8);
     case 16:
       if (p.waves == 12) GTS_LAUNCH(16, 12);
