@@ -117,9 +117,9 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
   // tiles fit in 64 KB (SHAP values, in double: 80 KB, two workgroups per CU),
   // or, if that would leave fewer than 8 rows per wave, 8 rows (then 4) using up
   // to the whole LDS of a workgroup.
+  const int longest = std::max(0, m->max_path_len - 1);
   auto need = [&](int rw, int waves, bool priv) {
-    // shared tiles of SHAP values hold doubles (TileT)
-    const size_t entry = INTER || priv || (rw == 4 && waves == 8) ? sizeof(T) : sizeof(double);
+    const size_t entry = wide_tile(rw, INTER, waves, priv, longest) ? sizeof(double) : sizeof(T);
     const size_t tiles = (size_t)rw * ((size_t)sx * sizeof(float) +
                                        (priv ? (size_t)waves : 1) * (size_t)sp * entry);
     const size_t stage = rw == 64 ? sizeof(Stage<T, false>) : sizeof(Stage<T, true>);
@@ -136,7 +136,7 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
     priv = true;
   } else {
     for (int cand : {64, 32, 16, 8}) {
-      const int w = cand == 64 && !INTER && m->max_path_len - 1 <= kQShort ? 12 : 8;
+      const int w = cand == 64 && !INTER && longest <= kQShort ? 12 : 8;
       const int64_t budget = INTER ? kSmallTile : kHalfCu;
       if ((int64_t)need(cand, w, false) <= std::min<int64_t>(budget, dev.lds_per_block)) {
         RW = cand;
@@ -164,11 +164,14 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
     if (!INTER && RW != 0 && RW <= 16) {
       const int cap = 24;
       int best = 0;
-      for (int w : {8, 12, 16}) {
+      for (int i = 0; i < 3; ++i) {
+        // at equal waves a CU, the larger workgroup: one X and phi tile for all
+        // (M = 300, paths of up to 8: 0.325 against 0.337 ms)
+        const int w = 16 - 4 * i;
         // 16 waves leave 128 registers, and fp64 paths of 13-16 features spill
         // much of a path's state there: 0.39 against 0.22 ms at 12 waves (M = 635,
         // 886 rows), 1.46 against 0.56 (M = 300, 2000 rows)
-        if (w == 16 && sizeof(T) == 8 && m->max_path_len - 1 > kQMid) continue;
+        if (w == 16 && sizeof(T) == 8 && longest > kQMid) continue;
         const int64_t n = need(RW, w, false);
         if (n > dev.lds_per_block) continue;
         const int per_cu = (int)std::min<int64_t>(cap, w * (dev.lds_per_cu / n));
@@ -234,11 +237,10 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
   plan.split_step = split_step;
   plan.tiles = tiles;
   // the kernel variant: the model's longest path, in features
-  const int qmax = std::max(0, m->max_path_len - 1);
-  plan.qmax = qmax <= kQShort ? kQShort
-              : (!INTER && qmax <= kMaxUnrolledShap) ? kQMid
-              : (!INTER && qmax <= kMaxUnrolledShapF64) ? kQExt
-                                                        : kQLong;
+  plan.qmax = longest <= kQShort ? kQShort
+              : (!INTER && longest <= kMaxUnrolledShap) ? kQMid
+              : (!INTER && longest <= kMaxUnrolledShapF64) ? kQExt
+                                                           : kQLong;
   return GTS_OK;
 }
 

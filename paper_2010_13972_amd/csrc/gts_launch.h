@@ -32,6 +32,12 @@ constexpr int kQMid = 12;
 constexpr int kQExt = 16;
 constexpr int kQLong = 64;
 
+// Whether a launch shape's phi tile holds doubles whatever the model's type (TileT
+// in gts_shap_kernel.h has the reasons).
+constexpr bool wide_tile(int rw, bool inter, int waves, bool priv, int qmax) {
+  return !inter && !priv && (rw >= 16 || (rw == 8 && waves > 8 && qmax > kQShort));
+}
+
 // Private-tile launches (64-row tiles, one path per wave) of models with at
 // most this many features keep rank tables of the row tile in LDS: per feature, the 64 row
 // keys in ascending order and, for every rank, the mask of the rows below it.

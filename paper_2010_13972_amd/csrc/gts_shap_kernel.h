@@ -171,8 +171,7 @@ __host__ __device__ constexpr double shapley_weight(int n, int k) {
 // waves, conflict-free): ds_add_f64 8 cycles and no result to wait for; ds_add_f32
 // 192 cycles, one lane at a time; a compare-and-swap on a float's bit pattern 14
 // cycles and a round trip of 200 (without a conflict the loop runs once).  So a
-// shared tile of SHAP values holds doubles for either dtype (TileT), and the
-// compare-and-swap remains for the tiles that only fit in float.
+// shared tile of SHAP values holds doubles where it can (TileT).
 __device__ __forceinline__ void lds_add(float* p, float v) {
   unsigned* q = reinterpret_cast<unsigned*>(p);
   unsigned old = *q, assumed;
@@ -198,12 +197,16 @@ template <> struct Bits<double> {
   static __device__ __forceinline__ double val(U u) { return __longlong_as_double((long long)u); }
 };
 
-// The type of the phi tile's entries: double for the shared tiles of SHAP values,
-// except 4 rows at 8 waves, the shape for phi rows too wide for a tile of doubles;
-// the model's type for private tiles (no atomics) and interaction values (the
-// tile's size decides the rows per workgroup there).
-template <typename T, int RW, bool INTER, int WAVES, bool PRIV>
-using TileT = std::conditional_t<!INTER && !PRIV && !(RW == 4 && WAVES == 8), double, T>;
+// The type of the phi tile's entries: double for the shared tiles of SHAP values of
+// 16 rows and more, and of 8 rows for paths of more than 8 features (whose registers
+// hold a CU to 16 waves whatever the tile; 784 features, paths of up to 16, 3000
+// rows: 0.55 against 0.78 ms in float).  The model's type for private tiles (no
+// atomics), interaction values (the tile's size decides the rows per workgroup
+// there), and the other tiles of 8 and 4 rows, where doubles would leave one
+// workgroup a CU (784 features, 10 classes, paths of up to 8, 10 000 rows: 7.0 ms
+// in double against 6.5).
+template <typename T, int RW, bool INTER, int WAVES, bool PRIV, int QMAX>
+using TileT = std::conditional_t<wide_tile(RW, INTER, WAVES, PRIV, QMAX), double, T>;
 
 // How a lane adds the contributions of one path to the phi tile.
 //   kExclusive  no other lane or wave updates these entries meanwhile (a
@@ -1006,7 +1009,7 @@ template <typename T, int RW, bool INTER, int WAVES, bool PRIV, int QMAX>
 __global__ __launch_bounds__(64 * WAVES) void shap_kernel(
     DevModel<T> d, const float* __restrict__ X, T* __restrict__ phi, Launch L) {
   extern __shared__ __align__(16) unsigned char smem[];
-  using A = TileT<T, RW, INTER, WAVES, PRIV>;
+  using A = TileT<T, RW, INTER, WAVES, PRIV, QMAX>;
   constexpr int kThreads = 64 * WAVES;
   const int M = d.M;
   const int G = d.G;
