@@ -104,3 +104,26 @@ def test_too_long_merged_path(torch):
     with pytest.raises(gts.GtsError) as dev:
         device_extract(torch, ens)
     assert dev.value.status == gts.GTS_EPATHLEN
+
+
+@pytest.mark.parametrize("M", [5, 90])
+@pytest.mark.parametrize("depth", [11, 12])
+def test_trees_around_one_workgroup(torch, M, depth):
+    """Full trees of 4095 and 8191 nodes, on both sides of the 4096 nodes one
+    workgroup holds, beside small ones, with at most and more than 64 features:
+    the host's elements and bias, byte for byte."""
+    w = synth.random_workload(40 + M, num_trees=2, max_depth=depth, p_split=1.0, M=M,
+                              num_groups=2, n_bg=300, rows=1)
+    small = synth.random_workload(41 + M, num_trees=9, max_depth=4, M=M, num_groups=2, n_bg=300,
+                                  rows=1)
+    a, b = w.ensemble, small.ensemble
+    cat = {k: np.concatenate([getattr(a, k), getattr(b, k)])
+           for k in ("tree_group", "left", "right", "feature", "threshold", "cover", "value")}
+    off = np.concatenate([a.tree_node_offsets, a.num_nodes + b.tree_node_offsets[1:]])
+    ens = synth.Ensemble(num_features=M, num_groups=2, tree_node_offsets=off, **cat)
+    assert np.diff(off).max() == (1 << (depth + 1)) - 1
+    raw, npaths, bias = gts.extract_paths_device(gts.DeviceEnsemble(ens))
+    el, want_paths, want_bias = gts.extract_paths(ens)
+    assert npaths == want_paths
+    assert raw.cpu().numpy().tobytes() == el.tobytes()
+    assert bias.cpu().numpy().tobytes() == want_bias.tobytes()
