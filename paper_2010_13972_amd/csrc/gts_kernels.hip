@@ -159,10 +159,10 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
     if (RW == 0 && (int64_t)need(8, 8, false) <= dev.lds_per_block) RW = 8;
     if (RW == 0 && (int64_t)need(4, 8, false) <= dev.lds_per_block) RW = 4;
     // Waves per workgroup for a shared tile of RW <= 16 rows: as many waves
-    // per CU as the LDS allows, up to 24 (the VGPR budget of the SHAP
-    // kernels).
+    // per CU as the LDS allows in whole workgroups, up to 24, or 16 (the registers
+    // of the fp32 kernel of short paths, and of the others).
     if (!INTER && RW != 0 && RW <= 16) {
-      const int cap = 24;
+      const int cap = sizeof(T) == 4 && longest <= kQShort ? 24 : 16;
       int best = 0;
       for (int i = 0; i < 3; ++i) {
         // at equal waves a CU, the larger workgroup: one X and phi tile for all
@@ -174,7 +174,7 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
         if (w == 16 && sizeof(T) == 8 && longest > kQMid) continue;
         const int64_t n = need(RW, w, false);
         if (n > dev.lds_per_block) continue;
-        const int per_cu = (int)std::min<int64_t>(cap, w * (dev.lds_per_cu / n));
+        const int per_cu = w * (int)std::min<int64_t>(cap / w, dev.lds_per_cu / n);
         if (per_cu > best) {
           best = per_cu;
           waves = w;
@@ -214,8 +214,15 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
     const int64_t target = 2 * per_cu * dev.cus;
     if (base < target) {
       int64_t want = (target + base - 1) / base;
+      // A slice with little to do spends its time on its tiles: with fewer than
+      // 4 bins a wave, one round of workgroups, of at least 4 bins each (100 trees
+      // of depth 8 over 54 features: 1 row 128 slices 13.8 us, 1024 34.7; 200 rows
+      // 128 18.7, 256 28.2; 1000 rows 32 32.8, 64 37.2).
+      if (bins_per_group < 4 * want * waves)
+        want = std::min(std::max<int64_t>(1, target / 2 / base),
+                        std::max<int64_t>(1, bins_per_group / 4));
       const int64_t step = 8 / std::gcd(G, 8);
-      want = (want + step - 1) / step * step;
+      if (want > 1) want = (want + step - 1) / step * step;
       const int64_t fine = std::min<int64_t>(128, bins_per_group / (8 * waves)) / step * step;
       min_splits = (int)std::max<int64_t>(1, std::min<int64_t>(want, bins_per_group));
       want = std::max(want, fine);
@@ -223,6 +230,14 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
       split_step = (int)step;
     }
     min_splits = std::min(min_splits, splits);
+  }
+  // The rank tables cost a workgroup about 0.7 us a feature and serve only models
+  // with zero fractions: they come with work enough to pay for them (1000 rows of
+  // 100 trees of depth 8 over 14 features, one or two bins a wave: 68.8 us with
+  // them, 32.6 without).  Without them the per-path test finds the dead paths.
+  if (rank_off != 0 && bins_per_group < (int64_t)kRankMinBins * splits * waves) {
+    rank_off = 0;
+    lds = need(RW, waves, priv);
   }
   plan.RW = RW;
   plan.waves = waves;

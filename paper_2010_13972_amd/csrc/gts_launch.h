@@ -39,10 +39,11 @@ constexpr bool wide_tile(int rw, bool inter, int waves, bool priv, int qmax) {
 }
 
 // Private-tile launches (64-row tiles, one path per wave) of models with at
-// most this many features keep rank tables of the row tile in LDS: per feature, the 64 row
+// most this many features, and bins enough for every wave, keep rank tables of the row tile in LDS: per feature, the 64 row
 // keys in ascending order and, for every rank, the mask of the rows below it.
 // They serve the dead-pair test of a whole bin at once.
 constexpr int kRankMaxM = 16;
+constexpr int kRankMinBins = 8;   // bins a wave
 inline size_t rank_table_bytes(int M) {
   return (size_t)M * 65 * (sizeof(uint64_t) + sizeof(int32_t));
 }
