@@ -536,7 +536,11 @@ constexpr double pow_n(double x, int n) {
 template <typename T, int Q, AddMode MODE, typename A>
 __device__ __forceinline__ void shap_math(const int (&f)[Q], const bool (&o)[Q], const T (&z)[Q],
                                           const bool (&on)[Q], T v, A* __restrict__ prow) {
-    constexpr int N = (Q + 1) / 2;
+  constexpr int N = (Q + 1) / 2;
+  // (1 - t)^(Q - 1) is 1.4e-9 at least for 8 features, times its node's weight, and
+  // 1.4e-27 for 16: there v comes in at the end, or leaves of 1e-12 would leave
+  // fp32's normal numbers
+  constexpr bool kLate = Q > kQShort;
   T of[Q], S[Q];
 #pragma unroll
   for (int k = 0; k < Q; ++k) {
@@ -547,7 +551,8 @@ __device__ __forceinline__ void shap_math(const int (&f)[Q], const bool (&o)[Q],
   for (int n = 0; n < N; ++n) {
     constexpr const double(&t)[8] = kGaussNode[N - 1];
     const T tau = T(t[n] / (1.0 - t[n]));
-    const T weight = v * T(kGaussWeight[N - 1][n] * pow_n(1.0 - t[n], Q - 1));
+    T weight = T(kGaussWeight[N - 1][n] * pow_n(1.0 - t[n], Q - 1));
+    if constexpr (!kLate) weight *= v;
     T a[Q], after[Q];
 #pragma unroll
     for (int k = 0; k < Q; ++k) a[k] = fma(of[k], tau, z[k]);
@@ -569,6 +574,7 @@ __device__ __forceinline__ void shap_math(const int (&f)[Q], const bool (&o)[Q],
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     val[i] = (of[i] - z[i]) * S[i];
+    if constexpr (kLate) val[i] *= v;
     // not sunk into a branch around the add
     if constexpr (MODE == kPaired) keep(val[i]);
     p[i] = prow + f[i];
