@@ -387,10 +387,13 @@ __global__ __launch_bounds__(kThreads) void k_tree(DevEnsemble e, Work w) {
   }
 }
 
-// Per reachable leaf: its path index; elements per path.
+// Per reachable leaf: its path index; elements per path.  Nothing once an error is
+// recorded: the ranks of a malformed tree are no indexes (a node that is both
+// children of its parent counts its leaves twice, a chain of such nodes once more
+// for each).
 __global__ void k_place(DevEnsemble e, Work w) {
   const int64_t gi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gi >= e.N) return;
+  if (gi >= e.N || w.err[0] != 0) return;
   const int32_t r = w.rank[gi];
   if (r < 0) return;
   const int64_t t = tree_of(e, gi);

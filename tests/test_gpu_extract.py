@@ -3,6 +3,8 @@ oracle's independent extraction (or_extract_paths) and against the host
 extraction gts_extract_paths: every element field and the bias compare as raw
 bytes.  Malformed ensembles, which the oracle does not validate, compare the
 error status with the host call's."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -95,6 +97,40 @@ def test_errors_match_the_host(torch):
         with pytest.raises(gts.GtsError) as dev:
             device_extract(torch, ens)
         assert dev.value.status == host.value.status == gts.GTS_EINVAL, what
+
+
+def doubled_chain(depth, below):
+    """A chain whose every node has the next one as both of its children, above a
+    full tree: a leaf's count of the leaves to its left grows past the number of
+    nodes, since every doubled link counts the whole tree once more."""
+    res = [(d + 1, d + 1, 0, 0.5, 16.0, 0.0) for d in range(depth)]
+    inner = (1 << below) - 1
+    for n in range(2 * inner + 1):
+        a = depth + 2 * n + 1
+        res.append((a, a + 1, 1, 0.5, 16.0, 0.0) if n < inner else (-1, -1, -1, 0.0, 1.0, 1.0))
+    ranks = depth * (inner + 1)
+    assert ranks > 8 * len(res)
+    return res
+
+
+def test_ranks_of_a_malformed_tree_are_not_used(torch):
+    """The ranks of such a tree would index far past the workspace: the call
+    reports the error as the host does, and a buffer allocated behind the
+    workspace keeps its bytes."""
+    ens = synth.ensemble_from_lists([doubled_chain(200, 8)], M=2)
+    dens = gts.DeviceEnsemble(ens)
+    size = ctypes.c_int64(0)
+    assert gts.lib().gts_extract_workspace_bytes(ens.num_trees, ens.num_nodes,
+                                                 ctypes.byref(size)) == 0
+    need = size.value
+    both = torch.full((need + (1 << 21),), 0x5a, dtype=torch.uint8, device="cuda")
+    say("device extraction doubled chain", ens.num_nodes, need)
+    with pytest.raises(gts.GtsError) as host:
+        gts.extract_paths(ens)
+    with pytest.raises(gts.GtsError) as dev:
+        gts.extract_paths_device(dens, workspace=both[:need])
+    assert dev.value.status == host.value.status == gts.GTS_EINVAL
+    assert bool((both[need:] == 0x5a).all())
 
 
 def test_too_long_merged_path(torch):
