@@ -28,6 +28,7 @@
 #include <vector>
 
 #include "gts_internal.h"
+#include "gts_launch.h"
 
 namespace gts {
 namespace {
@@ -300,7 +301,8 @@ __global__ __launch_bounds__(kThreads) void k_tree(DevEnsemble e, Work w) {
   __shared__ int16_t parent[kTreeNodes];
   __shared__ int32_t count[kTreeNodes];     // parents of a node, then leaves under it
   __shared__ int32_t feature[kTreeNodes];   // -1 on a leaf
-  const int64_t t = blockIdx.x;
+  const int64_t t = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  if (t >= e.T) return;   // the whole workgroup, before any barrier
   const int64_t base = e.off[t];
   const int32_t size = (int32_t)(e.off[t + 1] - base);
   for (int32_t n = threadIdx.x; n < size; n += kThreads) {
@@ -639,7 +641,8 @@ __device__ __forceinline__ double wave_ordered_sum(const double* __restrict__ x,
 template <typename I>
 __global__ void k_plan_tree_sums(const I* __restrict__ tree_paths, int64_t T,
                                  const double* __restrict__ term, double* __restrict__ tree_sum) {
-  const int64_t t = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const int64_t t = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * (blockDim.x >> 6) +
+                    (threadIdx.x >> 6);
   if (t >= T) return;
   const double s = wave_ordered_sum(term, tree_paths[t], tree_paths[t + 1], nullptr, 0);
   if ((threadIdx.x & 63) == 0) tree_sum[t] = s;
@@ -648,7 +651,8 @@ __global__ void k_plan_tree_sums(const I* __restrict__ tree_paths, int64_t T,
 // Per group (one wave): its trees' sums in tree order, in the blob's dtype.
 template <typename Z>
 __global__ void k_plan_bias(DevEnsemble e, const double* __restrict__ tree_sum, Z* __restrict__ bias) {
-  const int64_t g = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const int64_t g = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * (blockDim.x >> 6) +
+                    (threadIdx.x >> 6);
   if (g >= e.G) return;
   const double s = wave_ordered_sum(tree_sum, 0, e.T, e.group, (int32_t)g);
   if ((threadIdx.x & 63) == 0) bias[g] = (Z)s;
@@ -751,6 +755,12 @@ const char* describe(int code) {
   }
 }
 
+// One wave for each of n, kThreads / 64 of them in a workgroup.
+inline dim3 wave_grid(int64_t n) {
+  constexpr int kWaves = kThreads / 64;
+  return grid_of((n + kWaves - 1) / kWaves, kThreads);
+}
+
 inline unsigned blocks(int64_t n) { return (unsigned)std::max<int64_t>(1, (n + kThreads - 1) / kThreads); }
 
 }  // namespace
@@ -820,7 +830,7 @@ gts_status extract_device(const gts_ensemble* ens, gts_path_element* d_out, int6
     return fail(GTS_EINVAL, "tree %d: %s", err[1], describe(err[0]));
   const unsigned b = blocks(N);
   if (err[3] <= kTreeNodes) {
-    hipLaunchKernelGGL(k_tree, dim3((unsigned)T), dim3(kThreads), 0, s, e, w);
+    hipLaunchKernelGGL(k_tree, grid_of(T, kThreads), dim3(kThreads), 0, s, e, w);
   } else {
     hipLaunchKernelGGL(k_nodes, dim3(b), dim3(kThreads), 0, s, e, w);
     hipLaunchKernelGGL(k_count, dim3(b), dim3(kThreads), 0, s, e, w);
@@ -857,12 +867,10 @@ gts_status extract_device(const gts_ensemble* ens, gts_path_element* d_out, int6
   if (d_out == nullptr && d_bias == nullptr) return GTS_OK;
   hipLaunchKernelGGL(k_emit, dim3(blocks(P)), dim3(kThreads), 0, s, e, w, d_out, P);
   if (d_bias) {
-    constexpr int kWaves = kThreads / 64;
-    hipLaunchKernelGGL(k_plan_tree_sums<int64_t>, dim3((unsigned)((T + kWaves - 1) / kWaves)),
-                       dim3(kThreads), 0, s, w.tree_off, T, w.term, w.tree_sum);
-    hipLaunchKernelGGL(k_plan_bias<double>,
-                       dim3((unsigned)((ens->num_groups + kWaves - 1) / kWaves)), dim3(kThreads),
-                       0, s, e, w.tree_sum, d_bias);
+    hipLaunchKernelGGL(k_plan_tree_sums<int64_t>, wave_grid(T), dim3(kThreads), 0, s, w.tree_off,
+                       T, w.term, w.tree_sum);
+    hipLaunchKernelGGL(k_plan_bias<double>, wave_grid(ens->num_groups), dim3(kThreads), 0, s, e,
+                       w.tree_sum, d_bias);
   }
   if (hipGetLastError() != hipSuccess) return fail(GTS_EDEVICE, "kernel launch failed");
   return GTS_OK;
@@ -941,12 +949,10 @@ gts_status build_device(const gts_ensemble* ens, const gts_model* m, const gts_p
                        dirs, dest, tree_paths, P, m->num_elements, out, term);
   hipLaunchKernelGGL(k_plan_bins, dim3(blocks(std::max(K, G) + 1)), dim3(kThreads), 0, s, bins,
                      K, groups, G, out.bin_start, out.group_bins);
-  constexpr int kWaves = kThreads / 64;
   if (T > 0)
-    hipLaunchKernelGGL(k_plan_tree_sums<int32_t>, dim3((unsigned)((T + kWaves - 1) / kWaves)),
-                       dim3(kThreads), 0, s, tree_paths, T, term, tree_sum);
-  hipLaunchKernelGGL(k_plan_bias<Z>, dim3((unsigned)((G + kWaves - 1) / kWaves)),
-                     dim3(kThreads), 0, s, e, tree_sum, out.bias);
+    hipLaunchKernelGGL(k_plan_tree_sums<int32_t>, wave_grid(T), dim3(kThreads), 0, s, tree_paths,
+                       T, term, tree_sum);
+  hipLaunchKernelGGL(k_plan_bias<Z>, wave_grid(G), dim3(kThreads), 0, s, e, tree_sum, out.bias);
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) return fail(GTS_EDEVICE, "kernel launch failed: %s", hipGetErrorString(err));
   return GTS_OK;

@@ -242,7 +242,8 @@ __global__ __launch_bounds__(64 * WAVES) void inter_quad_kernel(DevModel<T> d,
   constexpr int kThreads = 64 * WAVES;
   constexpr int STRIDE = RW + 1;
   const int M = d.M, G = d.G, W = M + 1;
-  const int64_t b = blockIdx.x;
+  const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  if (b >= (int64_t)L.tiles * G * L.splits) return;   // the whole workgroup, before any barrier
   const int64_t tile = b % L.tiles;
   const int u = (int)(b / L.tiles);
   const int g = u / L.splits;
@@ -354,12 +355,6 @@ gts_status launch_quad(const KernelArgs& a, const Plan& p) {
   L.splits = p.splits;
   L.sx = p.sx;
   L.accumulate = p.splits > 1 ? 1 : 0;
-  const int64_t total = a.rows * (int64_t)m->num_groups * p.width;
-  if (L.accumulate) {
-    const int64_t blocks = std::min<int64_t>((total + 255) / 256, 65536);
-    hipLaunchKernelGGL(fill_zero<T>, dim3((unsigned)blocks), dim3(256), 0, stream,
-                       static_cast<T*>(a.phi), total);
-  }
   const int64_t grid = p.tiles * m->num_groups * p.splits;
   if (grid > 0x7fffffffLL) return fail(GTS_EINVAL, "problem too large for one launch");
   auto kern = inter_quad_kernel<T, A, RW, LPR, WAVES>;
@@ -368,7 +363,13 @@ gts_status launch_quad(const KernelArgs& a, const Plan& p) {
     (void)hipGetLastError();
     return fail(GTS_EDEVICE, "cannot set the LDS size of the kernel to %zu bytes", p.lds);
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * WAVES), p.lds, stream, d, a.X,
+  const int64_t total = a.rows * (int64_t)m->num_groups * p.width;
+  if (L.accumulate) {
+    const int64_t blocks = std::min<int64_t>((total + 255) / 256, 65536);
+    hipLaunchKernelGGL(fill_zero<T>, dim3((unsigned)blocks), dim3(256), 0, stream,
+                       static_cast<T*>(a.phi), total);
+  }
+  hipLaunchKernelGGL(kern, grid_of(grid, 64 * WAVES), dim3(64 * WAVES), p.lds, stream, d, a.X,
                      static_cast<T*>(a.phi), L);
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) return fail(GTS_EDEVICE, "kernel launch failed: %s", hipGetErrorString(err));

@@ -3,6 +3,9 @@
 // Not part of the public ABI.
 #pragma once
 
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 
@@ -65,6 +68,16 @@ struct Plan {
   bool quad = false;     // interactions by quadrature (gts_inter_quad.h)
   bool wide_tile = false;   // that kernel's tile in double for an fp32 model
 };
+
+// A grid of `total` workgroups.  A launch has fewer than 2^32 work-items in each
+// dimension, so the workgroups beyond go to further rows of the grid: workgroup b is
+// blockIdx.y * gridDim.x + blockIdx.x, and those from total on (the last row's end)
+// leave at once.
+constexpr int64_t kMaxWorkItems = 0xffffffffll;
+inline dim3 grid_of(int64_t total, int threads) {
+  const int64_t x = std::max<int64_t>(1, std::min<int64_t>(total, kMaxWorkItems / threads));
+  return dim3((unsigned)x, (unsigned)((total + x - 1) / x));
+}
 
 // Arguments of one gts_shap / gts_shap_interactions call.
 struct KernelArgs {

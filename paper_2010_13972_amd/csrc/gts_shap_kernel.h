@@ -1020,7 +1020,8 @@ __global__ __launch_bounds__(64 * WAVES) void shap_kernel(
   const int M = d.M;
   const int G = d.G;
   const int U = G * L.splits;
-  const int64_t b = blockIdx.x;
+  const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  if (b >= (int64_t)L.tiles * U) return;   // the whole workgroup, before any barrier
   int64_t tile;
   int u;
   if (U % 8 == 0) {
@@ -1145,7 +1146,7 @@ gts_status launch_rw(const KernelArgs& a, const Plan& p) {
   Launch L;
   L.rows = a.rows;
   L.ld = a.ld;
-  L.tiles = (int32_t)((a.rows + RW - 1) / RW);
+  L.tiles = (int32_t)p.tiles;
   L.splits = p.splits;
   L.sx = p.sx;
   L.sp = p.sp;
@@ -1156,13 +1157,7 @@ gts_status launch_rw(const KernelArgs& a, const Plan& p) {
   L.adaptive = (m->flags & GTS_MODEL_PRUNED) ? 1 : 0;
   L.min_splits = p.min_splits;
   L.split_step = p.split_step;
-  const int64_t total = a.rows * (int64_t)m->num_groups * p.width;
-  if (L.accumulate) {
-    const int64_t blocks = std::min<int64_t>((total + 255) / 256, 65536);
-    hipLaunchKernelGGL(fill_zero<T>, dim3((unsigned)blocks), dim3(256), 0, stream,
-                       static_cast<T*>(a.phi), total);
-  }
-  const int64_t grid = (int64_t)L.tiles * m->num_groups * p.splits;
+  const int64_t grid = p.tiles * m->num_groups * p.splits;
   if (grid > 0x7fffffffLL) return fail(GTS_EINVAL, "problem too large for one launch");
   auto kern = shap_kernel<T, RW, INTER, WAVES, PRIV, QMAX>;
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -1170,7 +1165,13 @@ gts_status launch_rw(const KernelArgs& a, const Plan& p) {
     (void)hipGetLastError();   // leave no error behind for the caller's next HIP call
     return fail(GTS_EDEVICE, "cannot set the LDS size of the kernel to %zu bytes", p.lds);
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * WAVES), p.lds, stream, d, a.X,
+  const int64_t total = a.rows * (int64_t)m->num_groups * p.width;
+  if (L.accumulate) {
+    const int64_t blocks = std::min<int64_t>((total + 255) / 256, 65536);
+    hipLaunchKernelGGL(fill_zero<T>, dim3((unsigned)blocks), dim3(256), 0, stream,
+                       static_cast<T*>(a.phi), total);
+  }
+  hipLaunchKernelGGL(kern, grid_of(grid, 64 * WAVES), dim3(64 * WAVES), p.lds, stream, d, a.X,
                      static_cast<T*>(a.phi), L);
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) return fail(GTS_EDEVICE, "kernel launch failed: %s", hipGetErrorString(err));
