@@ -14,24 +14,35 @@
 //   phi_ii = phi_i - sum_{j != i} Delta_ij = sum_n P rho_i (1 - (R - rho_i) / 2),
 // R = sum_k rho_k: one multiply-add per pair and node.  (The packed-path kernel
 // of gts_shap_kernel.h unwinds the path polynomial for every pair, with runtime
-// loops over arrays in private memory beyond 8 features: 10.9 ms for 200 rows of
-// 100 trees of depth 16 over 54 features, fp32, against 0.29 ms here.  Up to 8
+// loops over arrays in private memory beyond 8 features: 10.8 ms for 200 rows of
+// 100 trees of depth 16 over 54 features, fp32, against 0.31 ms here.  Up to 8
 // features its unrolled code is the faster one: 0.29 against 1.0 ms for 1000 rows
 // of 100 trees of depth 8 over 54 features.)
 //
 // Lanes.  A wave takes one path for RW rows; LPR neighbouring lanes share a row
 // and hold NPL = N / LPR nodes each.  The LPR lanes' partial sums of LPR entries
 // are exchanged by DPP so that every lane ends with one whole entry, and all 64
-// lanes add to the tile at once.  VALU issue bounds it (about 80 % of the SIMD
-// cycles at the size above), the pairs' multiply-adds and exchanges most of it.
+// lanes add to the tile at once.
 //
-// Tile.  A is the type of the tile's entries.  gfx950 adds doubles in LDS
-// natively (ds_add_f64, about 8 cycles per wave instruction and CU, no result to
-// wait for), floats only by compare-and-swap at a useful rate (14 cycles and a
-// round trip of 200; ds_add_f32: 192 cycles).  So an fp32 model's tile is in
-// double where 16 rows of it fit in LDS (M <= 38 or so); 8 rows in double
-// instead of 16 in float lose more than the adds gain (0.33 against 0.29 ms at
-// M = 54).
+// Tile and arithmetic.  A is the type of the tile's entries, C of the arithmetic.
+// The runtime-length code takes these paths in fp64 and adds to a tile of the
+// model's type; no launch here is further from fp64 values than it.
+//   C float, A double (fp32 models): the tile's sums are all but exact, which leaves
+//     the paths' own arithmetic.  Node pairs that fp32 holds (kPairC), a reciprocal
+//     with its remainder and a diagonal that holds phi_i until the tile is written,
+//     when the row's Delta_ij are taken from it, keep that small: 100 trees of depth
+//     14, 200 rows, distance from fp64 0.86e-7 at M = 40 (runtime-length code 1.59e-7),
+//     0.55e-7 at M = 54 (1.12e-7), 1.0e-7 at M = 77 (2.5e-7).  With rounded nodes and
+//     phi_ii formed path by path it was 1.13e-7 at M = 40, and with a float tile
+//     1.21e-7 at M = 54 and 2.75e-7 at M = 77, at 0.96 and 0.88 of the time.
+//   C double, A float (fp32 models of M >= 79, where 4 rows in double do not fit):
+//     phi_ii path by path, each entry rounded once per path, as the runtime-length
+//     code does.
+//   C and A double (fp64 models): phi_ii path by path too (from the tile 1.41e-15
+//     instead of 1.28e-15 from fp64 values, M = 29).
+// gfx950 adds doubles in LDS natively (ds_add_f64, about 8 cycles per wave
+// instruction and CU, no result to wait for), floats only by compare-and-swap at a
+// useful rate (14 cycles and a round trip of 200; ds_add_f32: 192 cycles).
 #pragma once
 
 #include "gts_shap_kernel.h"
@@ -42,19 +53,40 @@ namespace {
 constexpr int kQuadMaxQ = 16;
 constexpr int kQuadItems = kQuadMaxQ * (kQuadMaxQ + 1) / 2;   // entries of one path
 
-// Gauss-Legendre nodes and weights on [0, 1] for N = 4 and 8.
-__device__ const double kNodeT[2][8] = {
-    {0.069431844202973712388, 0.33000947820757186760, 0.66999052179242813240,
-     0.93056815579702628761},
-    {0.019855071751231884158, 0.10166676129318663020, 0.23723379504183550709,
-     0.40828267875217509753, 0.59171732124782490247, 0.76276620495816449291,
-     0.89833323870681336980, 0.98014492824876811584}};
-__device__ const double kNodeW[2][8] = {
-    {0.17392742256872692869, 0.32607257743127307131, 0.32607257743127307131,
-     0.17392742256872692869},
-    {0.050614268145188129576, 0.11119051722668723527, 0.15685332293894364367,
-     0.18134189168918099148, 0.18134189168918099148, 0.15685332293894364367,
-     0.11119051722668723527, 0.050614268145188129576}};
+// Node pairs of fp32 arithmetic, for N = 4 (set 0) and N = 8 (set 1) nodes.  A path's
+// polynomial is homogeneous in (c, t) = (1 - t, t), so any pair with the node's ratio
+// serves: a factor z c + o t is then the node's times S = c + t.  Rounded nodes would
+// move the products of all paths alike, by up to 16 errors of 3e-8; of the 2^23 floats
+// c from 1 - t up to its double, these are the ones for which t, 1 / c and 2 / S are all
+// within 2.5e-10 of a float.
+__device__ constexpr float kPairC[2][8] = {
+    {0x1.45f48p+0f, 0x1.7ca0ep-1f, 0x1.9dbfaep-2f, 0x1.74e742p-4f},
+    {0x1.07f282p+0f, 0x1.0eb69p+0f, 0x1.9675cp-1f, 0x1.4e90fap-1f, 0x1.9d6df6p-1f,
+     0x1.0d549ap-2f, 0x1.60516p-3f, 0x1.a20c36p-6f}};
+__device__ constexpr float kPairT[2][8] = {
+    {0x1.851fccp-4f, 0x1.76f6a6p-2f, 0x1.a3ffeap-1f, 0x1.385e12p+0f},
+    {0x1.5632dep-6f, 0x1.ea327cp-4f, 0x1.f9aa3cp-3f, 0x1.cdb2eep-2f, 0x1.2b969ap+0f,
+     0x1.b0fb88p-1f, 0x1.852338p+0f, 0x1.4273a4p+0f}};
+
+// Their weights over S^(Q - 2), the scale of P rho_i rho_j: [LPR == 8][(Q + 1) / 2][node],
+// Q = 1, 2, 4, ... 16 (four lanes a row run Q <= 8 on four nodes).
+struct PairWeights {
+  float w[2][9][8] = {};
+  constexpr PairWeights() {
+    for (int l = 0; l < 2; ++l)
+      for (int h = 0; h < 9; ++h) {
+        const int set = l == 0 && h <= 4 ? 0 : 1;
+        const int Q = h == 0 ? 1 : 2 * h;
+        for (int n = 0; n < (set ? 8 : 4); ++n) {
+          const double S = (double)kPairC[set][n] + (double)kPairT[set][n];
+          double x = kGaussWeight[set ? 7 : 3][n] * (Q == 1 ? S : 1.0);
+          for (int i = 2; i < Q; ++i) x /= S;
+          w[l][h][n] = (float)x;
+        }
+      }
+  }
+};
+__device__ constexpr PairWeights kPairWeights;
 
 // Per wave in LDS: the bin, and the tile entry of every pair of its current path.
 template <typename T>
@@ -113,46 +145,72 @@ __device__ __forceinline__ T scatter_sum(const T (&v)[LPR], int g) {
   }
 }
 
-template <typename T, int NPL>
+// A lane's nodes: factors are z c + o t, k = 1 / c, two = 2 / S, w = the weight (of fp32
+// arithmetic it depends on the path's length: kPairWeights).
+template <typename C, int NPL>
 struct Nodes {
   bool row;   // the lane has a row
-  T t[NPL], c[NPL], k[NPL], w[NPL];   // node, 1 - node, its reciprocal, weight
+  C t[NPL], c[NPL], k[NPL], two[NPL], w[NPL];
 };
 
+template <typename C, int NPL>
+__device__ __forceinline__ void set_node(Nodes<C, NPL>& nd, int i, int set, int n) {
+  if constexpr (sizeof(C) == 4) {
+    nd.c[i] = kPairC[set][n];
+    nd.t[i] = kPairT[set][n];
+    nd.k[i] = (C)(1.0 / (double)nd.c[i]);
+    nd.two[i] = (C)(2.0 / ((double)nd.c[i] + (double)nd.t[i]));
+    nd.w[i] = C(0);
+  } else {
+    const double t = kGaussNode[set ? 7 : 3][n];
+    nd.t[i] = t;
+    nd.c[i] = 1.0 - t;
+    nd.k[i] = 1.0 / (1.0 - t);
+    nd.two[i] = 2.0;
+    nd.w[i] = kGaussWeight[set ? 7 : 3][n];
+  }
+}
+
 // One path (root in slot s, q features, padded to Q) for the wave's rows.
-template <typename T, typename A, int Q, int NPL, int LPR, int STRIDE>
-__device__ __forceinline__ void quad_path(QuadStage<T>* st, int s, int q, const Nodes<T, NPL>& nd,
+template <typename T, typename C, typename A, int Q, int NPL, int LPR, int STRIDE>
+__device__ __forceinline__ void quad_path(QuadStage<T>* st, int s, int q, const Nodes<C, NPL>& nd,
+                                          const float* __restrict__ weights,
                                           const int* __restrict__ xrow, A* __restrict__ tile,
                                           const unsigned short* __restrict__ pairs, int lane,
                                           int W) {
+  constexpr bool kLater = sizeof(C) == 4;   // phi_ii is formed when the tile is written
   const int g = lane % LPR;
-  T P[NPL], R[NPL], rho[Q][NPL];
-  const T v = st->bin.w(s);
+  C P[NPL], R[NPL], rho[Q][NPL];
+  const C v = (C)st->bin.w(s);
 #pragma unroll
   for (int n = 0; n < NPL; ++n) {
-    P[n] = nd.w[n] * v;
-    R[n] = T(0);
+    if constexpr (sizeof(C) == 4) P[n] = weights[g * NPL + n] * v;
+    else P[n] = nd.w[n] * v;
+    R[n] = C(0);
   }
   bool live = nd.row;
 #pragma unroll
   for (int k = 0; k < Q; ++k) {
-    // past the path's end: z = 1 and present, a factor of 1 with rho = 0
+    // past the path's end: z = 1 and present, a factor of S with rho = 0
     const bool real = k < q;
     const int e = s + (real ? 1 + k : 0);
     const int4 head = st->bin.head[e];
-    const T z = real ? st->bin.z(e) : T(1);
+    const C z = real ? (C)st->bin.z(e) : C(1);
     const bool o = !real || in_range(xrow[real ? head.x : 0], head.y, (unsigned)head.z);
-    live &= o | (z != T(0));   // else a zero factor: the path leaves nothing here
-    const T d = T(1) - z;
+    live &= o | (z != C(0));   // else a zero factor: the path leaves nothing here
+    const C d = C(1) - z;
 #pragma unroll
     for (int n = 0; n < NPL; ++n) {
-      const T hi = fma(z, nd.c[n], nd.t[n]);
-      const T a = o ? hi : z * nd.c[n];
-      T r = d * recip(hi);
+      const C hi = fma(z, nd.c[n], nd.t[n]);
+      const C a = o ? hi : z * nd.c[n];
+      const C y = recip(hi);
+      C r = d * y;
+      // v_rcp_f32 leaves out up to one last bit: the remainder's share back
+      if constexpr (sizeof(C) == 4) r = fma(fma(-hi, r, d), y, r);
       keep(r);
       r = o ? r : -nd.k[n];
       P[n] *= a;
-      R[n] += r;
+      if constexpr (!kLater) R[n] += r;
       rho[k][n] = r;
     }
   }
@@ -173,26 +231,30 @@ __device__ __forceinline__ void quad_path(QuadStage<T>* st, int s, int q, const 
   constexpr int kItems = Q * (Q + 1) / 2;
   constexpr int kGroups = (kItems + LPR - 1) / LPR;
   constexpr int kBatch = 6;   // adds in flight
-  T part[LPR];
+  C part[LPR];
   A* p[kBatch];
   A val[kBatch];
   bool on[kBatch];
 #pragma unroll
   for (int j = 0; j < Q; ++j) {
-    T u[NPL];
+    C u[NPL];
 #pragma unroll
-    for (int n = 0; n < NPL; ++n) u[n] = T(0.5) * P[n] * rho[j][n];
+    for (int n = 0; n < NPL; ++n) u[n] = C(0.5) * P[n] * rho[j][n];
 #pragma unroll
     for (int i = 0; i <= j; ++i) {
       const int m = j * (j + 1) / 2 + i;
-      T x = T(0);
+      C x = C(0);
 #pragma unroll
       for (int n = 0; n < NPL; ++n)
-        x = fma(u[n], i < j ? rho[i][n] : T(2) - (R[n] - rho[j][n]), x);
+        x = fma(u[n],
+                i < j    ? rho[i][n]
+                : kLater ? nd.two[n]
+                         : nd.two[n] - (R[n] - rho[j][n]),
+                x);
       part[m % LPR] = x;
       if (m == kItems - 1) {
 #pragma unroll
-        for (int l = m % LPR + 1; l < LPR; ++l) part[l] = T(0);
+        for (int l = m % LPR + 1; l < LPR; ++l) part[l] = C(0);
       }
       if (m % LPR == LPR - 1 || m == kItems - 1) {
         const int grp = m / LPR;
@@ -210,16 +272,7 @@ __device__ __forceinline__ void quad_path(QuadStage<T>* st, int s, int q, const 
               on[l] = false;
             }
           }
-          if constexpr (sizeof(A) == 8) {
-            // native, without a result to wait for
-#pragma unroll
-            for (int l = 0; l < kBatch; ++l)
-              if (on[l])
-                __hip_atomic_fetch_add(p[l], val[l], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-          } else {
-            tile_add<kBatched>(p, val, on);
-          }
+          tile_add<kBatched>(p, val, on);
         }
       }
     }
@@ -233,12 +286,14 @@ __device__ __forceinline__ void quad_path(QuadStage<T>* st, int s, int q, const 
 // triangle of every row's block, entry by entry (rows of one entry are
 // neighbours, STRIDE = RW + 1 apart), so the lanes of one add fall on different
 // banks and so do the lanes of the final write.
-template <typename T, typename A, int RW, int LPR, int WAVES>
+template <typename T, typename C, typename A, int RW, int LPR, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void inter_quad_kernel(DevModel<T> d,
                                                                const float* __restrict__ X,
                                                                T* __restrict__ phi, Launch L) {
   extern __shared__ __align__(16) unsigned char smem[];
+  static_assert(sizeof(C) == 8 || sizeof(A) == 8, "fp32 arithmetic needs a tile in double");
   __shared__ unsigned short pairs[kQuadItems];
+  __shared__ float weights[sizeof(C) == 4 ? 9 * 8 : 1];
   constexpr int kThreads = 64 * WAVES;
   constexpr int STRIDE = RW + 1;
   const int M = d.M, G = d.G, W = M + 1;
@@ -266,6 +321,9 @@ __global__ __launch_bounds__(64 * WAVES) void inter_quad_kernel(DevModel<T> d,
     while ((j + 1) * (j + 2) / 2 <= i) ++j;
     pairs[i] = (unsigned short)((i - j * (j + 1) / 2) | j << 8);
   }
+  if constexpr (sizeof(C) == 4)
+    if (threadIdx.x < 9 * 8)
+      weights[threadIdx.x] = kPairWeights.w[LPR == 8][threadIdx.x / 8][threadIdx.x % 8];
   __syncthreads();
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -273,23 +331,13 @@ __global__ __launch_bounds__(64 * WAVES) void inter_quad_kernel(DevModel<T> d,
   // a tile of 4 rows leaves the upper half of the wave without rows
   const int r = (lane / LPR) % RW;
   const bool mine = lane / LPR < RW && r0 + r < L.rows;
-  Nodes<T, 8 / LPR> n8;
+  Nodes<C, 8 / LPR> n8;
   n8.row = mine;
-  Nodes<T, (LPR == 4 ? 1 : 8 / LPR)> n4;   // LPR == 8 runs all lengths on 8 nodes
+  Nodes<C, (LPR == 4 ? 1 : 8 / LPR)> n4;   // LPR == 8 runs all lengths on 8 nodes
 #pragma unroll
-  for (int n = 0; n < 8 / LPR; ++n) {
-    const double t = kNodeT[1][(lane % LPR) * (8 / LPR) + n];
-    n8.t[n] = (T)t;
-    n8.c[n] = (T)(1.0 - t);
-    n8.k[n] = (T)(1.0 / (1.0 - t));
-    n8.w[n] = (T)kNodeW[1][(lane % LPR) * (8 / LPR) + n];
-  }
+  for (int n = 0; n < 8 / LPR; ++n) set_node(n8, n, 1, (lane % LPR) * (8 / LPR) + n);
   if constexpr (LPR == 4) {
-    const double t = kNodeT[0][lane % LPR];
-    n4.t[0] = (T)t;
-    n4.c[0] = (T)(1.0 - t);
-    n4.k[0] = (T)(1.0 / (1.0 - t));
-    n4.w[0] = (T)kNodeW[0][lane % LPR];
+    set_node(n4, 0, 0, lane % LPR);
     n4.row = mine;
   } else {
     n4 = n8;
@@ -304,9 +352,11 @@ __global__ __launch_bounds__(64 * WAVES) void inter_quad_kernel(DevModel<T> d,
     for (uint64_t rest = ix.roots; rest != 0; rest &= rest - 1ull) {
       const int rl = __builtin_ctzll(rest);
       const int q = __builtin_amdgcn_readlane(ix.info, rl) & 0xff;
-#define GTS_QUAD(n, nd)                                                                     \
-  case n: quad_path<T, A, n, (int)(sizeof(nd.t) / sizeof(T)), LPR, STRIDE>(st, rl, q, nd, xrow, tp,    \
-                                                                 pairs, lane, W);            \
+#define GTS_QUAD(n, nd)                                                                      \
+  case n:                                                                                    \
+    quad_path<T, C, A, n, (int)(sizeof(nd.t) / sizeof(C)), LPR, STRIDE>(                     \
+        st, rl, q, nd, weights + (sizeof(C) == 4 ? (n / 2) * 8 : 0), xrow, tp, pairs, lane,  \
+        W);                                                                                  \
     break;
       switch (q <= 2 ? q : (q + 1) & ~1) {
         GTS_QUAD(1, n4) GTS_QUAD(2, n4) GTS_QUAD(4, n4) GTS_QUAD(6, n4) GTS_QUAD(8, n4)
@@ -319,6 +369,24 @@ __global__ __launch_bounds__(64 * WAVES) void inter_quad_kernel(DevModel<T> d,
     __builtin_amdgcn_wave_barrier();
   }
   __syncthreads();
+
+  if constexpr (sizeof(C) == 4) {
+    // phi_ii = phi_i - sum of Delta_ij: rows of one entry are neighbours, and the
+    // entries (j, f), j < f, lie W - 1 - j apart, then (f, j) one after the other
+    for (int i = threadIdx.x; i < RW * M; i += kThreads) {
+      const int f = i / RW, rr = i - f * RW;
+      A* const row = ps + rr;
+      A sum = row[(tri_row(f, W) + f) * STRIDE];
+      int at = f;
+      for (int j = 0; j < f; ++j) {
+        sum -= row[at * STRIDE];
+        at += W - 1 - j;
+      }
+      for (int j = f + 1; j < M; ++j) sum -= row[++at * STRIDE];
+      row[(tri_row(f, W) + f) * STRIDE] = sum;
+    }
+    __syncthreads();
+  }
 
   const T bias = s == 0 ? d.bias[g] : T(0);
   const int WW = W * W;
@@ -343,7 +411,7 @@ size_t quad_lds(int M, int rows, int waves, bool wide) {
   return tile + x + (size_t)waves * sizeof(QuadStage<T>);
 }
 
-template <typename T, typename A, int RW, int LPR, int WAVES>
+template <typename T, typename C, typename A, int RW, int LPR, int WAVES>
 gts_status launch_quad(const KernelArgs& a, const Plan& p) {
   const gts_model* m = a.m;
   hipStream_t stream = static_cast<hipStream_t>(a.stream);
@@ -357,7 +425,7 @@ gts_status launch_quad(const KernelArgs& a, const Plan& p) {
   L.accumulate = p.splits > 1 ? 1 : 0;
   const int64_t grid = p.tiles * m->num_groups * p.splits;
   if (grid > 0x7fffffffLL) return fail(GTS_EINVAL, "problem too large for one launch");
-  auto kern = inter_quad_kernel<T, A, RW, LPR, WAVES>;
+  auto kern = inter_quad_kernel<T, C, A, RW, LPR, WAVES>;
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds) != hipSuccess) {
     (void)hipGetLastError();
@@ -379,14 +447,18 @@ gts_status launch_quad(const KernelArgs& a, const Plan& p) {
 template <typename T>
 gts_status launch_quad_shape(const KernelArgs& a, const Plan& p) {
   if constexpr (sizeof(T) == 4) {
-    if (p.wide_tile) return launch_quad<T, double, 16, 4, 16>(a, p);
-    if (p.RW == 16) return launch_quad<T, float, 16, 4, 16>(a, p);
-    if (p.RW == 8) return launch_quad<T, float, 8, 8, 16>(a, p);
-    return launch_quad<T, float, 4, 8, 8>(a, p);
+    if (p.wide_tile) {
+      if (p.RW == 16) return launch_quad<T, float, double, 16, 4, 16>(a, p);
+      if (p.RW == 8) return launch_quad<T, float, double, 8, 8, 16>(a, p);
+      return launch_quad<T, float, double, 4, 8, 16>(a, p);
+    }
+    if (p.RW == 8) return launch_quad<T, double, float, 8, 8, 12>(a, p);
+    if (p.waves == 16) return launch_quad<T, double, float, 4, 8, 16>(a, p);
+    return launch_quad<T, double, float, 4, 8, 8>(a, p);
   } else {
-    if (p.RW == 16) return launch_quad<T, double, 16, 4, 8>(a, p);
-    if (p.RW == 8) return launch_quad<T, double, 8, 8, 8>(a, p);
-    return launch_quad<T, double, 4, 8, 8>(a, p);
+    if (p.RW == 16) return launch_quad<T, double, double, 16, 4, 8>(a, p);
+    if (p.RW == 8) return launch_quad<T, double, double, 8, 8, 8>(a, p);
+    return launch_quad<T, double, double, 4, 8, 8>(a, p);
   }
 }
 

@@ -55,9 +55,12 @@ DeviceInfo device_info() {
 inline int odd_at_least(int n) { return n | 1; }
 
 // Interaction values of paths of 9 to 16 features: the quadrature kernel, on the
-// largest tile of 16, 8 or 4 rows a workgroup's LDS holds; false where none fits
-// (then the runtime-length code runs, as for longer paths).  Slices as for the
-// other interaction launches: at most one round of workgroups.
+// largest tile of 16, 8 or 4 rows in double a workgroup's LDS holds, or, in fp32
+// models beyond 78 features, of 8 or 4 rows in float (200 rows of 100 trees of depth
+// 14: M = 82, 8 rows in float 1.22 ms, 4 in double, with 8 waves, 1.45); false where
+// none fits (beyond M = 118, fp64 81: then the runtime-length code runs, as for longer
+// paths).  Slices as for the other interaction launches: at most one round of
+// workgroups.
 template <typename T>
 bool plan_quad(const gts_model* m, int64_t rows, const DeviceInfo& dev, Plan& plan) {
   const int q = m->max_path_len - 1;
@@ -70,10 +73,11 @@ bool plan_quad(const gts_model* m, int64_t rows, const DeviceInfo& dev, Plan& pl
     int rw, waves;
     bool wide;   // tile in double (always for fp64 models)
   };
-  constexpr Shape f32[] = {{16, 16, true}, {16, 16, false}, {8, 16, false}, {4, 8, false}};
+  constexpr Shape f32[] = {{16, 16, true}, {8, 16, true},  {4, 16, true},
+                           {8, 12, false}, {4, 16, false}, {4, 8, false}};
   constexpr Shape f64[] = {{16, 8, true}, {8, 8, true}, {4, 8, true}};
   plan.RW = 0;
-  for (int i = 0; i < (sizeof(T) == 8 ? 3 : 4) && plan.RW == 0; ++i) {
+  for (int i = 0; i < (sizeof(T) == 8 ? 3 : 6) && plan.RW == 0; ++i) {
     const Shape& x = sizeof(T) == 8 ? f64[i] : f32[i];
     if ((int64_t)lds(x.rw, x.waves, x.wide) + kQuadStaticLds > dev.lds_per_block) continue;
     plan.RW = x.rw;

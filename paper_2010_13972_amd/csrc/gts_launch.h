@@ -25,7 +25,7 @@ constexpr int kMaxUnrolledShapF64 = 16;
 // Interaction values of paths of up to 16 features run by quadrature where the
 // model has longer ones than the unrolled code takes.
 constexpr int kMaxUnrolledQuad = 16;
-constexpr int64_t kQuadStaticLds = 512;   // that kernel's static LDS, rounded up
+constexpr int64_t kQuadStaticLds = 640;   // that kernel's static LDS, rounded up
 
 // Kernel variant by the model's longest path: every path has at most 8
 // features, at most 12, at most 16 (SHAP values only), or any length up to a

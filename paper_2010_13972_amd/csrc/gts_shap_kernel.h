@@ -481,7 +481,7 @@ __device__ __forceinline__ void unwind_one(const T (&E)[Q + 1], T zi, T (&D)[Q])
 // ---------------------------------------------------------------------------
 
 // Gauss-Legendre nodes and weights on [0, 1], row N - 1 for N = 1..8 nodes.
-constexpr double kGaussNode[8][8] = {
+__device__ constexpr double kGaussNode[8][8] = {
     {0.5},
     {0.21132486540518711775, 0.78867513459481288223},
     {0.11270166537925831149, 0.5, 0.88729833462074168848},
@@ -496,7 +496,7 @@ constexpr double kGaussNode[8][8] = {
     {0.01985507175123188417, 0.10166676129318663022, 0.23723379504183550708,
      0.40828267875217509752, 0.59171732124782490245, 0.76276620495816449292,
      0.89833323870681336978, 0.98014492824876811583}};
-constexpr double kGaussWeight[8][8] = {
+__device__ constexpr double kGaussWeight[8][8] = {
     {1},
     {0.5, 0.5},
     {0.27777777777777777778, 0.44444444444444444444, 0.27777777777777777778},

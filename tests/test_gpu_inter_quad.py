@@ -1,8 +1,8 @@
 """Interaction values of models whose longest path holds 9 to 16 features (the
 quadrature kernel), against the oracle's conditioning route: chains at every
-path length around its padded variants, and one model per tile shape (16, 8 and
-4 rows, tiles in float and in double), with shorter paths, zero covers, ties,
-several groups, ragged rows, a pruned model and rows that are not finite."""
+path length around its padded variants, and one model per tile shape, with
+shorter paths, zero covers, ties, several groups, ragged rows, a pruned model
+and rows that are not finite."""
 import numpy as np
 import pytest
 
@@ -38,24 +38,47 @@ def test_chains(torch, orc, depth, dtype):
     assert_parity(got, orc.interactions(ens, X), dtype, 2, what=f"chain {depth}")
 
 
-# (M, dtype, rows per tile of the launch)
-SHAPES = [(12, "f32", 16), (50, "f32", 16), (80, "f32", 8), (110, "f32", 4),
-          (20, "f64", 16), (50, "f64", 8), (75, "f64", 4)]
+# (M, dtype, rows per tile and waves of the launch): in fp32 tiles of 16, 8 and 4 rows
+# in double, then of 8 and 4 rows in float
+SHAPES = [(12, "f32", 16, 16), (50, "f32", 8, 16), (70, "f32", 4, 16), (80, "f32", 8, 12),
+          (110, "f32", 4, 16), (116, "f32", 4, 8),
+          (20, "f64", 16, 8), (50, "f64", 8, 8), (75, "f64", 4, 8)]
 
 
-@pytest.mark.parametrize("M,dtype,rw", SHAPES)
-def test_tile_shapes(torch, orc, M, dtype, rw):
+@pytest.mark.parametrize("M,dtype,rw,waves", SHAPES)
+def test_tile_shapes(torch, orc, M, dtype, rw, waves):
     w = synth.random_workload(900 + M, num_trees=9, max_depth=16, p_split=0.75, M=M, num_groups=3,
                               n_bg=60, rows=37, max_leaves=200)
     print("shape", M, dtype, rw, flush=True)
     model = gts.prepare(w.ensemble, dtype)
     assert 9 <= model.desc.max_path_len - 1 <= 16
-    assert gts.launch_config(model, 37, interactions=True)["rows_per_tile"] == rw
+    cfg = gts.launch_config(model, 37, interactions=True)
+    assert (cfg["rows_per_tile"], cfg["waves"]) == (rw, waves)
     want = orc.interactions(w.ensemble, w.X)
     assert_parity(run(torch, model, w.X), want, dtype, 2, what=f"M={M}")
     X = torch.from_numpy(w.X).cuda()
     pruned = gts.shap_interactions(gts.prune(model, X), X)
     assert_parity(pruned.cpu().numpy().astype(np.float64), want, dtype, 2, what=f"pruned M={M}")
+
+
+@pytest.mark.parametrize("M", [12, 30, 50, 56, 70, 77, 80, 110, 116])
+def test_no_further_from_fp64_than_the_runtime_length_code(torch, orc, M):
+    """The runtime-length code takes a path of 9 features and more in fp64 and rounds
+    once for each addition to a float tile.  Here the same blob runs through it when
+    the descriptor states a longest path beyond the quadrature's; the quadrature's
+    distance from the oracle is no larger."""
+    w = synth.random_workload(900 + M, num_trees=30, max_depth=16, p_split=0.85, M=M, num_groups=1,
+                              n_bg=300, rows=40, max_leaves=150)
+    model = gts.prepare(w.ensemble, "f32")
+    assert 9 <= model.desc.max_path_len - 1 <= 16
+    want = orc.interactions(w.ensemble, w.X)
+    quad = run(torch, model, w.X)
+    model.desc.max_path_len = 18
+    general = run(torch, model, w.X)
+    errs = [float(np.linalg.norm(x - want) / np.linalg.norm(want)) for x in (quad, general)]
+    print("distance", M, errs, flush=True)
+    assert not np.array_equal(quad, general)
+    assert errs[0] <= errs[1]
 
 
 def test_a_value_that_is_not_finite_is_in_no_range(torch):
