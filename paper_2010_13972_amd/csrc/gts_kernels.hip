@@ -59,8 +59,7 @@ inline int odd_at_least(int n) { return n | 1; }
 // models beyond 78 features, of 8 or 4 rows in float (200 rows of 100 trees of depth
 // 14: M = 82, 8 rows in float 1.22 ms, 4 in double, with 8 waves, 1.45); false where
 // none fits (beyond M = 118, fp64 81: then the runtime-length code runs, as for longer
-// paths).  Slices as for the other interaction launches: at most one round of
-// workgroups.
+// paths).  Slices: at most one round of workgroups.
 template <typename T>
 bool plan_quad(const gts_model* m, int64_t rows, const DeviceInfo& dev, Plan& plan) {
   const int q = m->max_path_len - 1;
@@ -92,9 +91,11 @@ bool plan_quad(const gts_model* m, int64_t rows, const DeviceInfo& dev, Plan& pl
   plan.width = (M + 1) * (M + 1);
   plan.tiles = (rows + plan.RW - 1) / plan.RW;
   const int64_t base = plan.tiles * G;
-  const int64_t per_cu = std::max<int64_t>(
-      1, std::min<int64_t>(32 / plan.waves, dev.lds_per_cu / (int64_t)(plan.lds + kQuadStaticLds)));
-  const int64_t round = per_cu * dev.cus;
+  // a CU holds one workgroup: 16 waves of 98 to 128 registers, 12 of 168, or 8 of 150
+  // and more; a second round of slices adds its tiles for nothing (M = 24, 200 trees,
+  // 40 rows: 85 slices 115 us, 170 135, 341 178; fp64, M = 12, 5 rows: 256 slices 62 us,
+  // 569 85)
+  const int64_t round = dev.cus;
   plan.splits = (int)std::max<int64_t>(
       1, std::min<int64_t>(round / base, std::max<int64_t>(1, m->num_bins / G / plan.waves)));
   plan.min_splits = plan.splits;

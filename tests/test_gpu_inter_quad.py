@@ -81,6 +81,21 @@ def test_no_further_from_fp64_than_the_runtime_length_code(torch, orc, M):
     assert errs[0] <= errs[1]
 
 
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("rows", [40, 100, 300])
+def test_slices_of_one_round(torch, rows, dtype):
+    """A CU's registers hold one workgroup: the slices of a model with bins enough come
+    to one workgroup for each CU at most."""
+    w = synth.random_workload(12, num_trees=60, max_depth=14, p_split=0.9, M=12, n_bg=500, rows=1,
+                              max_leaves=256)
+    model = gts.prepare(w.ensemble, dtype)
+    assert 9 <= model.desc.max_path_len - 1 <= 16
+    cfg = gts.launch_config(model, rows, interactions=True)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert model.desc.num_bins // cfg["waves"] * (-(-rows // 16)) > cus   # bins for more
+    assert cus // 2 < cfg["workgroups"] <= cus
+
+
 def test_a_value_that_is_not_finite_is_in_no_range(torch):
     """NaN and +inf fail every element's range test: a row of either gives what
     the other gives, finite everywhere, and the rows beside it are unchanged."""
