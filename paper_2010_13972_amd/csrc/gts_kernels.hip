@@ -117,14 +117,10 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
   const int32_t sp = odd_at_least(INTER ? (int32_t)((int64_t)(M + 1) * (M + 2) / 2) : width);
   // Row tile and accumulation.  If 64 rows with a private phi tile for each
   // of 4 waves fit in 64 KB of LDS, use them (no contention, no atomics).
-  // Otherwise 8 waves share one tile (12 for SHAP values of short paths on 64
-  // rows, whose 64 registers leave room for 24 waves a CU): the largest RW whose
-  // tiles fit in 64 KB (SHAP values, in double: 80 KB, two workgroups per CU),
-  // or, if that would leave fewer than 8 rows per wave, 8 rows (then 4) using up
-  // to the whole LDS of a workgroup.
+  // Otherwise the waves of a workgroup share one tile.
   const int longest = std::max(0, m->max_path_len - 1);
-  auto need = [&](int rw, int waves, bool priv) {
-    const size_t entry = wide_tile(rw, INTER, waves, priv, longest) ? sizeof(double) : sizeof(T);
+  auto need = [&](int rw, int waves, bool priv, bool wide) {
+    const size_t entry = wide ? sizeof(double) : sizeof(T);
     const size_t tiles = (size_t)rw * ((size_t)sx * sizeof(float) +
                                        (priv ? (size_t)waves : 1) * (size_t)sp * entry);
     const size_t stage = rw == 64 ? sizeof(Stage<T, false>) : sizeof(Stage<T, true>);
@@ -133,41 +129,62 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
   int RW = 0;
   int waves = 8;
   bool priv = false;
+  bool wide = false;
   constexpr int64_t kSmallTile = 64 * 1024;  // leaves room for several workgroups per CU
   constexpr int64_t kHalfCu = 80 * 1024;     // two workgroups per CU
-  if ((int64_t)need(64, 4, true) <= std::min<int64_t>(kSmallTile, dev.lds_per_block)) {
+  const int64_t whole = dev.lds_per_block;
+  // takes the shape where it fits and none is taken yet
+  auto take = [&](int rw, int w, bool in_double, int64_t budget) {
+    if (RW != 0 || (int64_t)need(rw, w, false, in_double) > std::min(budget, whole)) return;
+    RW = rw;
+    waves = w;
+    wide = in_double;
+  };
+  if ((int64_t)need(64, 4, true, false) <= std::min(kSmallTile, whole)) {
     RW = 64;
     waves = 4;
     priv = true;
+  } else if (INTER) {
+    // Interaction values: 8 waves on the largest tile of 64 KB; else 16 (the
+    // kernel's registers allow one workgroup of them per CU) on the largest of 16,
+    // 8 or 4 rows a workgroup's LDS holds.
+    for (int rw : {64, 32, 16, 8}) take(rw, 8, false, kSmallTile);
+    for (int rw : {16, 8, 4}) take(rw, 16, false, whole);
+    take(4, 8, false, whole);
   } else {
-    for (int cand : {64, 32, 16, 8}) {
-      const int w = cand == 64 && !INTER && longest <= kQShort ? 12 : 8;
-      const int64_t budget = INTER ? kSmallTile : kHalfCu;
-      if ((int64_t)need(cand, w, false) <= std::min<int64_t>(budget, dev.lds_per_block)) {
-        RW = cand;
-        waves = w;
-        break;
-      }
-    }
-    if (INTER && RW == 0) {
-      // Interaction values: 16 waves (the kernel's registers allow one
-      // workgroup of them per CU) on the largest tile of 16, 8 or 4 rows the
-      // LDS of a workgroup holds.
-      for (int cand : {16, 8, 4}) {
-        if ((int64_t)need(cand, 16, false) <= dev.lds_per_block) {
-          RW = cand;
-          waves = 16;
-          break;
-        }
-      }
-    }
-    if (RW == 0 && (int64_t)need(8, 8, false) <= dev.lds_per_block) RW = 8;
-    if (RW == 0 && (int64_t)need(4, 8, false) <= dev.lds_per_block) RW = 4;
-    // Waves per workgroup for a shared tile of RW <= 16 rows: as many waves
+    // SHAP values: the largest tile of which a CU holds two, in double also for fp32
+    // models (native adds).  8 waves, or 12 for short paths on 64 rows, whose 64
+    // registers leave room for 24 waves a CU.
+    constexpr bool kWide = sizeof(T) == 4;
+    const bool is_short = longest <= kQShort;
+    if (is_short) take(64, 12, kWide, kHalfCu);
+    if (kWide || !is_short) take(64, 8, kWide, kHalfCu);
+    // The doubles' size alone would halve the rows, and with 64 of them lose the
+    // one-path form, of fp32 models whose tile in float takes 64 KB: one workgroup of
+    // 16 waves keeps them (10 000 rows, 64 rows against 32: M = 95, paths of 8
+    // features, 303 us against 342, of 11 1029 against 1161; 32 against 16: M = 180,
+    // of 11 1286 against 1729, of 16 1832 against 2395; 16 rows of short paths run
+    // 24 waves a CU and win there, 355 against 430; 16 against 8: M = 373, of 16 2619
+    // against 2842, of 11 2034 against 1973).  64 and 32 rows not for paths beyond 16
+    // features, whose loops are faster on fewer: M = 95, 3000 rows, 64 rows 4.75 ms, 32
+    // 3.91 (M = 350, 16 rows 5.4 in float, 8 8.9).
+    const bool unrolled = longest <= kMaxUnrolledShapF64;
+    if (kWide && unrolled && (int64_t)need(64, 8, false, false) <= kSmallTile)
+      take(64, 16, true, whole);
+    take(32, 8, kWide, kHalfCu);
+    if (kWide && unrolled && !is_short && (int64_t)need(32, 8, false, false) <= kSmallTile)
+      take(32, 16, true, whole);
+    take(16, 8, kWide, kHalfCu);
+    if (kWide && longest > kQMid && (int64_t)need(16, 8, false, false) <= kSmallTile)
+      take(16, 16, true, whole);
+    take(8, 8, false, kHalfCu);
+    take(8, 8, false, whole);
+    take(4, 8, false, whole);
+    // Waves per workgroup for a tile of RW <= 16 rows: as many waves
     // per CU as the LDS allows in whole workgroups, up to 24, or 16 (the registers
     // of the fp32 kernel of short paths, and of the others).
-    if (!INTER && RW != 0 && RW <= 16) {
-      const int cap = sizeof(T) == 4 && longest <= kQShort ? 24 : 16;
+    if (RW != 0 && RW <= 16) {
+      const int cap = sizeof(T) == 4 && is_short ? 24 : 16;
       int best = 0;
       for (int i = 0; i < 3; ++i) {
         // at equal waves a CU, the larger workgroup: one X and phi tile for all
@@ -177,18 +194,24 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
         // much of a path's state there: 0.39 against 0.22 ms at 12 waves (M = 635,
         // 886 rows), 1.46 against 0.56 (M = 300, 2000 rows)
         if (w == 16 && sizeof(T) == 8 && longest > kQMid) continue;
-        const int64_t n = need(RW, w, false);
-        if (n > dev.lds_per_block) continue;
+        // 8 rows in double: for the longer paths, whose registers hold a CU to 16
+        // waves whatever the tile (784 features, paths of up to 16, 3000 rows: 0.55
+        // against 0.78 ms in float); 10 classes, paths of up to 8, 10 000 rows: 7.0 ms
+        // in double against 6.5
+        const bool d = kWide && (RW == 16 || (RW == 8 && w > 8 && !is_short));
+        const int64_t n = need(RW, w, false, d);
+        if (n > whole) continue;
         const int per_cu = w * (int)std::min<int64_t>(cap / w, dev.lds_per_cu / n);
         if (per_cu > best) {
           best = per_cu;
           waves = w;
+          wide = d;
         }
       }
     }
   }
   if (RW == 0) return fail(GTS_EINVAL, "M = %d needs more LDS than a workgroup has", M);
-  size_t lds = need(RW, waves, priv);
+  size_t lds = need(RW, waves, priv, wide);
   // rank tables for the bin-wide dead-pair test of one-path-per-wave launches
   size_t rank_off = 0;
   if (RW == 64 && priv && M <= kRankMaxM) {
@@ -242,11 +265,12 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
   // them, 32.6 without).  Without them the per-path test finds the dead paths.
   if (rank_off != 0 && bins_per_group < (int64_t)kRankMinBins * splits * waves) {
     rank_off = 0;
-    lds = need(RW, waves, priv);
+    lds = need(RW, waves, priv, wide);
   }
   plan.RW = RW;
   plan.waves = waves;
   plan.priv = priv;
+  plan.wide_tile = wide;
   plan.sx = sx;
   plan.sp = sp;
   plan.width = width;

@@ -35,10 +35,17 @@ constexpr int kQMid = 12;
 constexpr int kQExt = 16;
 constexpr int kQLong = 64;
 
-// Whether a launch shape's phi tile holds doubles whatever the model's type (TileT
-// in gts_shap_kernel.h has the reasons).
-constexpr bool wide_tile(int rw, bool inter, int waves, bool priv, int qmax) {
-  return !inter && !priv && (rw >= 16 || (rw == 8 && waves > 8 && qmax > kQShort));
+// The shared-tile launch shapes of a kernel variant that the planner gives: rows,
+// waves, and whether the tile holds doubles whatever the model's type.
+constexpr bool has_shape(bool f64, bool inter, int qmax, int rw, int waves, bool wide) {
+  if (inter) return !wide && (waves == 8 || (waves == 16 && rw <= 16));
+  const bool longer = qmax > kQShort;
+  if (f64) return !wide && (rw <= 16 || waves == 8 || (rw == 64 && waves == 12 && !longer));
+  if (rw == 64) return wide && (waves == 8 || (waves == 12 && !longer) || (waves == 16 && qmax <= kQExt));
+  if (rw == 32) return wide && (waves == 8 || (waves == 16 && longer && qmax <= kQExt));
+  if (rw == 16) return wide;
+  if (rw == 8) return !wide || (waves > 8 && longer);
+  return !wide;
 }
 
 // Private-tile launches (64-row tiles, one path per wave) of models with at
@@ -66,7 +73,7 @@ struct Plan {
   int qmax = kQLong;
   size_t rank_off = 0;   // LDS offset of the rank tables (0: none)
   bool quad = false;     // interactions by quadrature (gts_inter_quad.h)
-  bool wide_tile = false;   // that kernel's tile in double for an fp32 model
+  bool wide_tile = false;   // the tile in double for an fp32 model
 };
 
 // A grid of `total` workgroups.  A launch has fewer than 2^32 work-items in each

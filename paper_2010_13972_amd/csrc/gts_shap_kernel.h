@@ -197,16 +197,11 @@ template <> struct Bits<double> {
   static __device__ __forceinline__ double val(U u) { return __longlong_as_double((long long)u); }
 };
 
-// The type of the phi tile's entries: double for the shared tiles of SHAP values of
-// 16 rows and more, and of 8 rows for paths of more than 8 features (whose registers
-// hold a CU to 16 waves whatever the tile; 784 features, paths of up to 16, 3000
-// rows: 0.55 against 0.78 ms in float).  The model's type for private tiles (no
-// atomics), interaction values (the tile's size decides the rows per workgroup
-// there), and the other tiles of 8 and 4 rows, where doubles would leave one
-// workgroup a CU (784 features, 10 classes, paths of up to 8, 10 000 rows: 7.0 ms
-// in double against 6.5).
-template <typename T, int RW, bool INTER, int WAVES, bool PRIV, int QMAX>
-using TileT = std::conditional_t<wide_tile(RW, INTER, WAVES, PRIV, QMAX), double, T>;
+// The type of the phi tile's entries: double, whatever the model's type, in the wide
+// launches (shared tiles of SHAP values, where the planner finds room), else the
+// model's type.
+template <typename T, bool WIDE>
+using TileT = std::conditional_t<WIDE, double, T>;
 
 // How a lane adds the contributions of one path to the phi tile.
 //   kExclusive  no other lane or wave updates these entries meanwhile (a
@@ -1011,11 +1006,11 @@ __device__ __forceinline__ void process_bin(Stage<T, RW < 64>* st, const Bin<T>&
 // tiles; otherwise the grid is unit-major, all XCDs working through one
 // unit's row tiles together.  Either way each XCD's L2 holds about one
 // unit's bins at a time.
-template <typename T, int RW, bool INTER, int WAVES, bool PRIV, int QMAX>
+template <typename T, int RW, bool INTER, int WAVES, bool PRIV, int QMAX, bool WIDE>
 __global__ __launch_bounds__(64 * WAVES) void shap_kernel(
     DevModel<T> d, const float* __restrict__ X, T* __restrict__ phi, Launch L) {
   extern __shared__ __align__(16) unsigned char smem[];
-  using A = TileT<T, RW, INTER, WAVES, PRIV, QMAX>;
+  using A = TileT<T, WIDE>;
   constexpr int kThreads = 64 * WAVES;
   const int M = d.M;
   const int G = d.G;
@@ -1138,7 +1133,7 @@ __global__ void fill_zero(T* __restrict__ p, int64_t n) {
 // launch of one variant
 // ---------------------------------------------------------------------------
 
-template <typename T, int RW, bool INTER, int WAVES, bool PRIV, int QMAX>
+template <typename T, int RW, bool INTER, int WAVES, bool PRIV, int QMAX, bool WIDE>
 gts_status launch_rw(const KernelArgs& a, const Plan& p) {
   const gts_model* m = a.m;
   hipStream_t stream = static_cast<hipStream_t>(a.stream);
@@ -1159,7 +1154,7 @@ gts_status launch_rw(const KernelArgs& a, const Plan& p) {
   L.split_step = p.split_step;
   const int64_t grid = p.tiles * m->num_groups * p.splits;
   if (grid > 0x7fffffffLL) return fail(GTS_EINVAL, "problem too large for one launch");
-  auto kern = shap_kernel<T, RW, INTER, WAVES, PRIV, QMAX>;
+  auto kern = shap_kernel<T, RW, INTER, WAVES, PRIV, QMAX, WIDE>;
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds) != hipSuccess) {
     (void)hipGetLastError();   // leave no error behind for the caller's next HIP call
@@ -1178,27 +1173,37 @@ gts_status launch_rw(const KernelArgs& a, const Plan& p) {
   return GTS_OK;
 }
 
+// The kernel of one launch shape, where the planner gives it (has_shape).
+template <typename T, bool INTER, int QMAX, int RW, int WAVES, bool WIDE>
+bool try_shape(const KernelArgs& a, const Plan& p, gts_status& st) {
+  if constexpr (has_shape(sizeof(T) == 8, INTER, QMAX, RW, WAVES, WIDE)) {
+    if (p.RW == RW && p.waves == WAVES && p.wide_tile == WIDE) {
+      st = launch_rw<T, RW, INTER, WAVES, false, QMAX, WIDE>(a, p);
+      return true;
+    }
+  }
+  return false;
+}
+
+template <typename T, bool INTER, int QMAX, int RW>
+bool try_rows(const KernelArgs& a, const Plan& p, gts_status& st) {
+  return try_shape<T, INTER, QMAX, RW, 8, false>(a, p, st) ||
+         try_shape<T, INTER, QMAX, RW, 12, false>(a, p, st) ||
+         try_shape<T, INTER, QMAX, RW, 16, false>(a, p, st) ||
+         try_shape<T, INTER, QMAX, RW, 8, true>(a, p, st) ||
+         try_shape<T, INTER, QMAX, RW, 12, true>(a, p, st) ||
+         try_shape<T, INTER, QMAX, RW, 16, true>(a, p, st);
+}
+
 template <typename T, bool INTER, int QMAX>
 gts_status launch_shape(const KernelArgs& a, const Plan& p) {
-  if (p.priv) return launch_rw<T, 64, INTER, 4, true, QMAX>(a, p);
-#define GTS_LAUNCH(rw, w) return launch_rw<T, rw, INTER, w, false, QMAX>(a, p)
-  switch (p.RW) {
-    case 64: GTS_LAUNCH(64, (INTER || QMAX > kQShort ? 8 : 12));
-    case 32: GTS_LAUNCH(32, 8);
-    case 16:
-      if (p.waves == 12) GTS_LAUNCH(16, 12);
-      if (p.waves == 16) GTS_LAUNCH(16, 16);
-      GTS_LAUNCH(16, 8);
-    case 8:
-      if (p.waves == 12) GTS_LAUNCH(8, 12);
-      if (p.waves == 16) GTS_LAUNCH(8, 16);
-      GTS_LAUNCH(8, 8);
-    default:
-      if (p.waves == 12) GTS_LAUNCH(4, 12);
-      if (p.waves == 16) GTS_LAUNCH(4, 16);
-      GTS_LAUNCH(4, 8);
-  }
-#undef GTS_LAUNCH
+  if (p.priv) return launch_rw<T, 64, INTER, 4, true, QMAX, false>(a, p);
+  gts_status st = GTS_OK;
+  if (try_rows<T, INTER, QMAX, 64>(a, p, st) || try_rows<T, INTER, QMAX, 32>(a, p, st) ||
+      try_rows<T, INTER, QMAX, 16>(a, p, st) || try_rows<T, INTER, QMAX, 8>(a, p, st) ||
+      try_rows<T, INTER, QMAX, 4>(a, p, st))
+    return st;
+  return fail(GTS_EDEVICE, "no kernel of %d rows and %d waves", p.RW, p.waves);
 }
 
 // The variant for the model's longest path.

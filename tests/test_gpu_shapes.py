@@ -1,0 +1,40 @@
+"""Shared-tile launch shapes of SHAP values around the planner's lines, each against
+Algorithm 1 on a ragged row count, with the rows and waves the planner gives."""
+import numpy as np
+import pytest
+
+from paper_2010_13972_amd import gts, synth
+from parity import assert_parity
+from test_gpu_shap import chain_tree
+
+pytestmark = pytest.mark.gpu
+
+# (features, dtype, longest path, rows per tile, waves)
+SHAPES = [
+    # 64 rows in double: two workgroups of 12 or 8 waves a CU, one of 16
+    (80, "f32", 8, 64, 12), (81, "f32", 8, 64, 8), (95, "f32", 8, 64, 16), (102, "f32", 8, 64, 16),
+    (103, "f32", 8, 32, 8), (81, "f32", 11, 64, 8), (95, "f32", 11, 64, 16),
+    (102, "f32", 16, 64, 16), (102, "f32", 20, 32, 8), (103, "f32", 11, 32, 8),
+    # 32 rows: the same
+    (166, "f32", 11, 32, 8), (167, "f32", 11, 32, 16), (186, "f32", 16, 32, 16),
+    (186, "f32", 20, 16, 16),
+    # 16 rows: the same, beyond 12 features
+    (333, "f32", 13, 16, 16), (334, "f32", 13, 16, 16), (373, "f32", 20, 16, 16),
+    (334, "f32", 12, 8, 16), (374, "f32", 13, 8, 16),
+]
+
+
+@pytest.mark.parametrize("M,dtype,q,rows,waves", SHAPES)
+def test_shape(orc, M, dtype, q, rows, waves):
+    import torch
+    rng = np.random.default_rng(M + q)
+    m = min(M, 63)
+    ens = synth.ensemble_from_lists([chain_tree(q, m, rng), chain_tree(max(1, q - 3), m, rng)], M=M)
+    X = rng.random((71, M)).astype(np.float32)
+    model = gts.prepare(ens, dtype)
+    assert model.desc.max_path_len == q + 1
+    cfg = gts.launch_config(model, 71)
+    print("shape", M, dtype, q, cfg, flush=True)
+    assert (cfg["rows_per_tile"], cfg["waves"], cfg["private_tiles"]) == (rows, waves, 0)
+    got = gts.shap(model, torch.from_numpy(X).cuda()).cpu().numpy().astype(np.float64)
+    assert_parity(got, orc.treeshap(ens, X), dtype, what=f"M={M} {dtype} {q} features")

@@ -9,8 +9,8 @@ import pytest
 
 REPORT = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
                       "paper_2010_13972_amd", "_build", "kernel_resources.txt")
-# shap_kernel<T, RW, INTER, WAVES, PRIV, QMAX> in the mangled name
-KERNEL = re.compile(r"shap_kernelI([fd])Li(\d+)ELb(\d)ELi(\d+)ELb(\d)ELi(\d+)E")
+# shap_kernel<T, RW, INTER, WAVES, PRIV, QMAX, WIDE> in the mangled name
+KERNEL = re.compile(r"shap_kernelI([fd])Li(\d+)ELb(\d)ELi(\d+)ELb(\d)ELi(\d+)ELb(\d)E")
 
 
 def variants():
@@ -22,18 +22,38 @@ def variants():
             d = dict(kv.split("=", 1) for kv in line.rstrip("\n").split("\t"))
             m = KERNEL.search(d["name"])
             if m:
-                t, rw, inter, waves, priv, qmax = m.groups()
+                t, rw, inter, waves, priv, qmax, wide = m.groups()
                 out.append(dict(dtype=t, rw=int(rw), inter=inter == "1", waves=int(waves),
-                                priv=priv == "1", qmax=int(qmax),
+                                priv=priv == "1", qmax=int(qmax), wide=wide == "1",
                                 scratch=int(d["ScratchSize [bytes/lane]"]),
                                 vgprs=int(d["VGPRs"])))
     return out
 
 
+def planned(dtype, inter, qmax):
+    """The launch shapes the planner gives a variant: (rows, waves, private, double)."""
+    def of(rows, waves, wide=False):
+        return {(rows, w, False, wide) for w in waves}
+    out = {(64, 4, True, False)}
+    if inter:
+        return out | of(64, [8]) | of(32, [8]) | of(16, [8, 16]) | of(8, [8, 16]) | of(4, [8, 16])
+    low = of(8, [8, 12, 16]) | of(4, [8, 12, 16])
+    if dtype == "d":
+        return out | low | of(64, [8, 12] if qmax == 8 else [8]) | of(32, [8]) | of(16, [8, 12, 16])
+    out |= low | of(16, [8, 12, 16], True)
+    out |= of(64, {8: [8, 12, 16], 64: [8]}.get(qmax, [8, 16]), True)
+    out |= of(32, {8: [8], 64: [8]}.get(qmax, [8, 16]), True)
+    return out if qmax == 8 else out | of(8, [12, 16], True)
+
+
 def test_every_variant_is_built():
     v = variants()
-    # 12 launch shapes x (4 SHAP + 2 interaction variants) x 2 dtypes
-    assert len(v) == 12 * 6 * 2
+    for dtype in "fd":
+        for inter, lengths in ((False, (8, 12, 16, 64)), (True, (8, 64))):
+            for qmax in lengths:
+                built = [(x["rw"], x["waves"], x["priv"], x["wide"]) for x in v
+                         if (x["dtype"], x["inter"], x["qmax"]) == (dtype, inter, qmax)]
+                assert sorted(built) == sorted(planned(dtype, inter, qmax)), (dtype, inter, qmax)
     assert {x["qmax"] for x in v if not x["inter"]} == {8, 12, 16, 64}
     assert {x["qmax"] for x in v if x["inter"]} == {8, 64}
 
@@ -81,7 +101,7 @@ def test_headline_variants_fit_their_occupancy():
             cap = 80 if x["priv"] else 64
             assert x["vgprs"] <= cap and x["scratch"] == 0, x
             seen += 1
-    assert seen == 2
+    assert seen == 4   # the private tile; shared ones of 8, 12 and 16 waves
 
 
 def test_prune_kernels_use_no_private_memory():
