@@ -174,7 +174,13 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
     take(32, 8, kWide, kHalfCu);
     if (kWide && unrolled && !is_short && (int64_t)need(32, 8, false, false) <= kSmallTile)
       take(32, 16, true, whole);
-    take(16, 8, kWide, kHalfCu);
+    // Short fp32 paths: 24 waves a CU on as many rows as two workgroups of 12 hold in
+    // double, 16 to M = 287, then 8 to 576 (100 trees of depth 8, 10 000 rows: M = 333,
+    // 8 rows 446 us, 16 rows of which a CU holds one workgroup 505; M = 373, 436, 8 rows in
+    // float 558; 16 rows in float 441 and 439).
+    if (kWide && is_short) take(16, 12, true, kHalfCu);
+    if (kWide && is_short) take(8, 12, true, kHalfCu);
+    if (!kWide || !is_short) take(16, 8, kWide, kHalfCu);
     if (kWide && longest > kQMid && (int64_t)need(16, 8, false, false) <= kSmallTile)
       take(16, 16, true, whole);
     take(8, 8, false, kHalfCu);
@@ -183,7 +189,7 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
     // Waves per workgroup for a tile of RW <= 16 rows: as many waves
     // per CU as the LDS allows in whole workgroups, up to 24, or 16 (the registers
     // of the fp32 kernel of short paths, and of the others).
-    if (RW != 0 && RW <= 16) {
+    if (RW != 0 && RW <= 16 && !(wide && is_short)) {
       const int cap = sizeof(T) == 4 && is_short ? 24 : 16;
       int best = 0;
       for (int i = 0; i < 3; ++i) {

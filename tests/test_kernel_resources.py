@@ -40,10 +40,10 @@ def planned(dtype, inter, qmax):
     low = of(8, [8, 12, 16]) | of(4, [8, 12, 16])
     if dtype == "d":
         return out | low | of(64, [8, 12] if qmax == 8 else [8]) | of(32, [8]) | of(16, [8, 12, 16])
-    out |= low | of(16, [8, 12, 16], True)
+    out |= low | of(16, [12] if qmax == 8 else [8, 12, 16], True)
     out |= of(64, {8: [8, 12, 16], 64: [8]}.get(qmax, [8, 16]), True)
     out |= of(32, {8: [8], 64: [8]}.get(qmax, [8, 16]), True)
-    return out if qmax == 8 else out | of(8, [12, 16], True)
+    return out | of(8, [12] if qmax == 8 else [12, 16], True)
 
 
 def test_every_variant_is_built():
