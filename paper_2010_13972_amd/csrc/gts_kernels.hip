@@ -200,11 +200,12 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
         // much of a path's state there: 0.39 against 0.22 ms at 12 waves (M = 635,
         // 886 rows), 1.46 against 0.56 (M = 300, 2000 rows)
         if (w == 16 && sizeof(T) == 8 && longest > kQMid) continue;
-        // 8 rows in double: for the longer paths, whose registers hold a CU to 16
-        // waves whatever the tile (784 features, paths of up to 16, 3000 rows: 0.55
-        // against 0.78 ms in float); 10 classes, paths of up to 8, 10 000 rows: 7.0 ms
-        // in double against 6.5
-        const bool d = kWide && (RW == 16 || (RW == 8 && w > 8 && !is_short));
+        // In double where that fits; 8 rows for longer paths only, whose registers hold
+        // a CU to 16 waves whatever the tile (784 features, paths of up to 16, 3000 rows:
+        // 0.55 against 0.78 ms in float), and 16 waves in float before 12 or 8 in double
+        // (700 rows of 60 trees, M = 1800: 16 waves 0.18 ms, 8 0.35).
+        const bool d = kWide && (RW == 16 || (RW == 8 && w > 8 && !is_short)) &&
+                       (int64_t)need(RW, w, false, true) <= whole;
         const int64_t n = need(RW, w, false, d);
         if (n > whole) continue;
         const int per_cu = w * (int)std::min<int64_t>(cap / w, dev.lds_per_cu / n);

@@ -44,7 +44,7 @@ constexpr bool has_shape(bool f64, bool inter, int qmax, int rw, int waves, bool
   if (rw == 64) return wide && (waves == 8 || (waves == 12 && !longer) || (waves == 16 && qmax <= kQExt));
   if (rw == 32) return wide && (waves == 8 || (waves == 16 && longer && qmax <= kQExt));
   if (rw == 16) return wide && (longer || waves == 12);
-  if (rw == 8) return !wide || (longer ? waves > 8 : waves == 12);
+  if (rw == 8) return !wide || waves == (longer ? 16 : 12);
   return !wide;
 }
 

@@ -21,6 +21,9 @@ SHAPES = [
     # 16 rows: the same, beyond 12 features
     (333, "f32", 13, 16, 16), (334, "f32", 13, 16, 16), (373, "f32", 20, 16, 16),
     (334, "f32", 12, 8, 16), (374, "f32", 13, 8, 16),
+    # 8 rows: 16 waves in double, then in float
+    (1337, "f32", 11, 8, 16), (1338, "f32", 11, 8, 16), (1430, "f32", 16, 8, 16),
+    (2007, "f32", 20, 8, 16), (2008, "f32", 11, 8, 12),
     # short paths: 12 waves twice a CU, on 16 and 8 rows in double, then in float
     (167, "f32", 8, 16, 12), (287, "f32", 8, 16, 12), (288, "f32", 8, 8, 12),
     (373, "f32", 8, 8, 12), (576, "f32", 8, 8, 12), (577, "f32", 8, 8, 12),

@@ -43,7 +43,7 @@ def planned(dtype, inter, qmax):
     out |= low | of(16, [12] if qmax == 8 else [8, 12, 16], True)
     out |= of(64, {8: [8, 12, 16], 64: [8]}.get(qmax, [8, 16]), True)
     out |= of(32, {8: [8], 64: [8]}.get(qmax, [8, 16]), True)
-    return out | of(8, [12] if qmax == 8 else [12, 16], True)
+    return out | of(8, [12] if qmax == 8 else [16], True)
 
 
 def test_every_variant_is_built():
