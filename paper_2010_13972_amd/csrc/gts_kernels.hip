@@ -187,19 +187,20 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
     take(8, 8, false, whole);
     take(4, 8, false, whole);
     // Waves per workgroup for a tile of RW <= 16 rows: as many waves
-    // per CU as the LDS allows in whole workgroups, up to 24, or 16 (the registers
-    // of the fp32 kernel of short paths, and of the others).
+    // per CU as the LDS allows in whole workgroups, up to what the registers of the
+    // variant allow: 24 (77 of them, fp32, short paths), one workgroup (fp64, longer
+    // ones: 177 and more for 8 waves, 168 for 12, 128 for 16), else 16.
     if (RW != 0 && RW <= 16 && !(wide && is_short)) {
-      const int cap = sizeof(T) == 4 && is_short ? 24 : 16;
+      const int cap = kWide && is_short ? 24 : 16;
       int best = 0;
       for (int i = 0; i < 3; ++i) {
         // at equal waves a CU, the larger workgroup: one X and phi tile for all
         // (M = 300, paths of up to 8: 0.325 against 0.337 ms)
         const int w = 16 - 4 * i;
-        // 16 waves leave 128 registers, and fp64 paths of 13-16 features spill
-        // much of a path's state there: 0.39 against 0.22 ms at 12 waves (M = 635,
-        // 886 rows), 1.46 against 0.56 (M = 300, 2000 rows)
-        if (w == 16 && sizeof(T) == 8 && longest > kQMid) continue;
+        // 16 waves leave 128 registers, and fp64 paths of 11 features and more spill
+        // there: 3000 rows of 100 trees, 12 waves against 16, of 12 features 1.19 against
+        // 1.69 ms (M = 300), of 16 1.98 against 3.20 (M = 635); of 10, 0.75 against 0.68
+        if (w == 16 && sizeof(T) == 8 && longest > 10) continue;
         // In double where that fits; 8 rows for longer paths only, whose registers hold
         // a CU to 16 waves whatever the tile (784 features, paths of up to 16, 3000 rows:
         // 0.55 against 0.78 ms in float), and 16 waves in float before 12 or 8 in double
@@ -208,7 +209,8 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
                        (int64_t)need(RW, w, false, true) <= whole;
         const int64_t n = need(RW, w, false, d);
         if (n > whole) continue;
-        const int per_cu = w * (int)std::min<int64_t>(cap / w, dev.lds_per_cu / n);
+        const int groups = kWide || is_short ? cap / w : 1;
+        const int per_cu = w * (int)std::min<int64_t>(groups, dev.lds_per_cu / n);
         if (per_cu > best) {
           best = per_cu;
           waves = w;

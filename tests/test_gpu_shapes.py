@@ -27,6 +27,11 @@ SHAPES = [
     # short paths: 12 waves twice a CU, on 16 and 8 rows in double, then in float
     (167, "f32", 8, 16, 12), (287, "f32", 8, 16, 12), (288, "f32", 8, 8, 12),
     (373, "f32", 8, 8, 12), (576, "f32", 8, 8, 12), (577, "f32", 8, 8, 12),
+    # fp64: 16 waves to 10 features, then 12, whose registers hold a path
+    (160, "f64", 9, 16, 16), (300, "f64", 10, 8, 16), (160, "f64", 11, 16, 12),
+    (285, "f64", 12, 16, 12), (300, "f64", 12, 8, 12),
+    (635, "f64", 16, 8, 12), (784, "f64", 20, 8, 12), (1300, "f64", 12, 8, 8),
+    (1500, "f64", 16, 4, 12),
 ]
 
 

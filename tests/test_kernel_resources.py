@@ -37,10 +37,11 @@ def planned(dtype, inter, qmax):
     out = {(64, 4, True, False)}
     if inter:
         return out | of(64, [8]) | of(32, [8]) | of(16, [8, 16]) | of(8, [8, 16]) | of(4, [8, 16])
-    low = of(8, [8, 12, 16]) | of(4, [8, 12, 16])
     if dtype == "d":
-        return out | low | of(64, [8, 12] if qmax == 8 else [8]) | of(32, [8]) | of(16, [8, 12, 16])
-    out |= low | of(16, [12] if qmax == 8 else [8, 12, 16], True)
+        low = [8, 12, 16] if qmax <= 12 else [8, 12]
+        out |= of(16, low) | of(8, low) | of(4, low)
+        return out | of(64, [8, 12] if qmax == 8 else [8]) | of(32, [8])
+    out |= of(8, [8, 12, 16]) | of(4, [8, 12, 16]) | of(16, [12] if qmax == 8 else [8, 12, 16], True)
     out |= of(64, {8: [8, 12, 16], 64: [8]}.get(qmax, [8, 16]), True)
     out |= of(32, {8: [8], 64: [8]}.get(qmax, [8, 16]), True)
     return out | of(8, [12] if qmax == 8 else [16], True)
