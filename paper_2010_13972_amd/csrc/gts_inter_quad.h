@@ -297,10 +297,10 @@ __global__ __launch_bounds__(64 * WAVES) void inter_quad_kernel(DevModel<T> d,
   constexpr int kThreads = 64 * WAVES;
   constexpr int STRIDE = RW + 1;
   const int M = d.M, G = d.G, W = M + 1;
-  const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-  if (b >= (int64_t)L.tiles * G * L.splits) return;   // the whole workgroup, before any barrier
-  const int64_t tile = b % L.tiles;
-  const int u = (int)(b / L.tiles);
+  const unsigned b = blockIdx.y * L.grid_x + blockIdx.x;
+  if (b >= L.groups) return;   // the whole workgroup, before any barrier
+  const int64_t tile = b % (unsigned)L.tiles;
+  const int u = (int)(b / (unsigned)L.tiles);
   const int g = u / L.splits;
   const int s = u - g * L.splits;
   const int64_t r0 = tile * RW;
@@ -437,7 +437,10 @@ gts_status launch_quad(const KernelArgs& a, const Plan& p) {
     hipLaunchKernelGGL(fill_zero<T>, dim3((unsigned)blocks), dim3(256), 0, stream,
                        static_cast<T*>(a.phi), total);
   }
-  hipLaunchKernelGGL(kern, grid_of(grid, 64 * WAVES), dim3(64 * WAVES), p.lds, stream, d, a.X,
+  const dim3 dims = grid_of(grid, 64 * WAVES);
+  L.grid_x = dims.x;
+  L.groups = (uint32_t)grid;
+  hipLaunchKernelGGL(kern, dims, dim3(64 * WAVES), p.lds, stream, d, a.X,
                      static_cast<T*>(a.phi), L);
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) return fail(GTS_EDEVICE, "kernel launch failed: %s", hipGetErrorString(err));

@@ -148,6 +148,9 @@ struct Launch {
   int32_t adaptive;
   int32_t min_splits;
   int32_t split_step;
+  // The grid, as grid_of lays it out: workgroups in a row, and in all.
+  uint32_t grid_x;
+  uint32_t groups;
 };
 
 // Makes v a value the compiler must hold in registers at this point, so the
@@ -1015,20 +1018,22 @@ __global__ __launch_bounds__(64 * WAVES) void shap_kernel(
   const int M = d.M;
   const int G = d.G;
   const int U = G * L.splits;
-  const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-  if (b >= (int64_t)L.tiles * U) return;   // the whole workgroup, before any barrier
-  int64_t tile;
+  // 32 bits: fewer than 2^31 workgroups and a row of the grid
+  const unsigned b = blockIdx.y * L.grid_x + blockIdx.x;
+  if (b >= L.groups) return;   // the whole workgroup, before any barrier
+  unsigned row_tile;
   int u;
   if (U % 8 == 0) {
-    const int64_t local = b >> 3;
-    tile = local % L.tiles;
-    u = (int)(b & 7) + 8 * (int)(local / L.tiles);
+    const unsigned local = b >> 3;
+    row_tile = local % (unsigned)L.tiles;
+    u = (int)(b & 7) + 8 * (int)(local / (unsigned)L.tiles);
   } else {
     // unit-major: the XCDs work through one unit's row tiles together, so
     // each L2 holds the bins of about one unit at a time
-    tile = b % L.tiles;
-    u = (int)(b / L.tiles);
+    row_tile = b % (unsigned)L.tiles;
+    u = (int)(b / (unsigned)L.tiles);
   }
+  const int64_t tile = row_tile;
   const int g = u / L.splits;
   const int s = u - g * L.splits;
   const int64_t r0 = tile * RW;
@@ -1166,7 +1171,10 @@ gts_status launch_rw(const KernelArgs& a, const Plan& p) {
     hipLaunchKernelGGL(fill_zero<T>, dim3((unsigned)blocks), dim3(256), 0, stream,
                        static_cast<T*>(a.phi), total);
   }
-  hipLaunchKernelGGL(kern, grid_of(grid, 64 * WAVES), dim3(64 * WAVES), p.lds, stream, d, a.X,
+  const dim3 dims = grid_of(grid, 64 * WAVES);
+  L.grid_x = dims.x;
+  L.groups = (uint32_t)grid;
+  hipLaunchKernelGGL(kern, dims, dim3(64 * WAVES), p.lds, stream, d, a.X,
                      static_cast<T*>(a.phi), L);
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) return fail(GTS_EDEVICE, "kernel launch failed: %s", hipGetErrorString(err));
