@@ -153,12 +153,15 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
     take(4, 8, false, whole);
   } else {
     // SHAP values: the largest tile of which a CU holds two, in double also for fp32
-    // models (native adds).  8 waves, or 12 for short paths on 64 rows, whose 64
-    // registers leave room for 24 waves a CU.
+    // models (native adds).  8 waves, or 12 for short fp32 paths on 64 rows, whose 64
+    // registers leave room for 24 waves a CU.  fp64 kernels of short paths have 110, for
+    // 16 waves: 8 there (3000 rows of 100 trees, M = 45: 8 waves 111 us, 12 131), and 32
+    // rows from 70 KB on (M = 69), for the sake of small batches (M = 75, 60 rows: 21 us
+    // against 29 with 64; 5000 rows: 433 against 359).
     constexpr bool kWide = sizeof(T) == 4;
     const bool is_short = longest <= kQShort;
-    if (is_short) take(64, 12, kWide, kHalfCu);
-    if (kWide || !is_short) take(64, 8, kWide, kHalfCu);
+    if (kWide && is_short) take(64, 12, kWide, kHalfCu);
+    take(64, 8, kWide, kWide || !is_short ? kHalfCu : 70 * 1024);
     // The doubles' size alone would halve the rows, and with 64 of them lose the
     // one-path form, of fp32 models whose tile in float takes 64 KB: one workgroup of
     // 16 waves keeps them (10 000 rows, 64 rows against 32: M = 95, paths of 8

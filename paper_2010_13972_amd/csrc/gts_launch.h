@@ -41,7 +41,7 @@ constexpr bool has_shape(bool f64, bool inter, int qmax, int rw, int waves, bool
   if (inter) return !wide && (waves == 8 || (waves == 16 && rw <= 16));
   const bool longer = qmax > kQShort;
   if (f64 && rw <= 16) return !wide && (waves < 16 || qmax <= kQMid);
-  if (f64) return !wide && (waves == 8 || (rw == 64 && waves == 12 && !longer));
+  if (f64) return !wide && waves == 8;
   if (rw == 64) return wide && (waves == 8 || (waves == 12 && !longer) || (waves == 16 && qmax <= kQExt));
   if (rw == 32) return wide && (waves == 8 || (waves == 16 && longer && qmax <= kQExt));
   if (rw == 16) return wide && (longer || waves == 12);

@@ -27,6 +27,9 @@ SHAPES = [
     # short paths: 12 waves twice a CU, on 16 and 8 rows in double, then in float
     (167, "f32", 8, 16, 12), (287, "f32", 8, 16, 12), (288, "f32", 8, 8, 12),
     (373, "f32", 8, 8, 12), (576, "f32", 8, 8, 12), (577, "f32", 8, 8, 12),
+    # fp64: 8 waves on 64 and 32 rows
+    (40, "f64", 8, 64, 8), (68, "f64", 8, 64, 8), (69, "f64", 8, 32, 8), (81, "f64", 9, 64, 8),
+    (82, "f64", 9, 32, 8), (142, "f64", 12, 32, 8),
     # fp64: 16 waves to 10 features, then 12, whose registers hold a path
     (160, "f64", 9, 16, 16), (300, "f64", 10, 8, 16), (160, "f64", 11, 16, 12),
     (285, "f64", 12, 16, 12), (300, "f64", 12, 8, 12),

@@ -40,7 +40,7 @@ def planned(dtype, inter, qmax):
     if dtype == "d":
         low = [8, 12, 16] if qmax <= 12 else [8, 12]
         out |= of(16, low) | of(8, low) | of(4, low)
-        return out | of(64, [8, 12] if qmax == 8 else [8]) | of(32, [8])
+        return out | of(64, [8]) | of(32, [8])
     out |= of(8, [8, 12, 16]) | of(4, [8, 12, 16]) | of(16, [12] if qmax == 8 else [8, 12, 16], True)
     out |= of(64, {8: [8, 12, 16], 64: [8]}.get(qmax, [8, 16]), True)
     out |= of(32, {8: [8], 64: [8]}.get(qmax, [8, 16]), True)
