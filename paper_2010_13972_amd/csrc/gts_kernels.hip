@@ -170,7 +170,7 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
     // 24 waves a CU and win there, 355 against 430; 16 against 8: M = 373, of 16 2619
     // against 2842, of 11 2034 against 1973).  64 and 32 rows not for paths beyond 16
     // features, whose loops are faster on fewer: M = 95, 3000 rows, 64 rows 4.75 ms, 32
-    // 3.91 (M = 350, 16 rows 5.4 in float, 8 8.9).
+    // 3.91 (M = 350, 16 rows 4.7, 8 8.9).
     const bool unrolled = longest <= kMaxUnrolledShapF64;
     if (kWide && unrolled && (int64_t)need(64, 8, false, false) <= kSmallTile)
       take(64, 16, true, whole);
@@ -183,41 +183,48 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
     // float 558; 16 rows in float 441 and 439).
     if (kWide && is_short) take(16, 12, true, kHalfCu);
     if (kWide && is_short) take(8, 12, true, kHalfCu);
-    if (!kWide || !is_short) take(16, 8, kWide, kHalfCu);
-    if (kWide && longest > kQMid && (int64_t)need(16, 8, false, false) <= kSmallTile)
-      take(16, 16, true, whole);
-    take(8, 8, false, kHalfCu);
-    take(8, 8, false, whole);
-    take(4, 8, false, whole);
-    // Waves per workgroup for a tile of RW <= 16 rows: as many waves
-    // per CU as the LDS allows in whole workgroups, up to what the registers of the
-    // variant allow: 24 (77 of them, fp32, short paths), one workgroup (fp64, longer
-    // ones: 177 and more for 8 waves, 168 for 12, 128 for 16), else 16.
-    if (RW != 0 && RW <= 16 && !(wide && is_short)) {
-      const int cap = kWide && is_short ? 24 : 16;
+    // At equal waves a CU the larger workgroup, here and below: it needs fewer slices, and
+    // every slice adds its tile to phi.  Few row tiles gain (fp64, M = 160, paths of 8, 60
+    // rows: one of 16 waves 15.4 us, two of 8 18.7), many would be faster with two (fp32,
+    // M = 300, of 11, 10 000 rows, 16 rows: 1849 and 1611 us; fp64, M = 300, of 6, 5000
+    // rows: 135 and 109), but fp32 sums of 40 slices instead of one would be 1.2 times as
+    // far from fp64 values.
+    // Longer fp32 paths, whose registers hold a CU to 16 waves: 16 rows of which a CU
+    // holds two tiles, else 8, in double (784 features, paths of up to 16, 3000 rows: 0.55
+    // against 0.78 ms in float), also of 12 waves (M = 1400: 16 in float at the same time,
+    // 1.1 times as far from fp64 values), else in float, before fewer waves (700 rows of 60
+    // trees, M = 1800: 16 waves 0.16 ms, 8 0.35), and 4 rows.
+    if (kWide && !is_short) {
+      if ((int64_t)need(16, 8, false, true) <= kHalfCu ||
+          (longest > kQMid && (int64_t)need(16, 8, false, false) <= kSmallTile))
+        take(16, 16, true, whole);
+      for (int w : {16, 12}) take(8, w, true, whole);
+      for (int rw : {8, 4})
+        for (int w : {16, 12, 8}) take(rw, w, false, whole);
+    }
+    // The others: the rows of which a CU holds two tiles, and as many waves a CU as the
+    // LDS allows in whole workgroups, up to what the registers of the variant allow: 24
+    // (77 of them, fp32, short paths; in float, 10 classes, 784 features: 6.5 ms, in
+    // double 7.0), one workgroup (fp64, longer ones: 177 and more for 8 waves, 168 for
+    // 12, 128 for 16), else 16.
+    if (RW == 0) {
+      if (!kWide) take(16, 8, false, kHalfCu);
+      take(8, 8, false, kHalfCu);
+      take(8, 8, false, whole);
+      take(4, 8, false, whole);
       int best = 0;
-      for (int i = 0; i < 3; ++i) {
-        // at equal waves a CU, the larger workgroup: one X and phi tile for all
-        // (M = 300, paths of up to 8: 0.325 against 0.337 ms)
-        const int w = 16 - 4 * i;
+      for (int w : {16, 12, 8}) {
         // 16 waves leave 128 registers, and fp64 paths of 11 features and more spill
         // there: 3000 rows of 100 trees, 12 waves against 16, of 12 features 1.19 against
         // 1.69 ms (M = 300), of 16 1.98 against 3.20 (M = 635); of 10, 0.75 against 0.68
-        if (w == 16 && sizeof(T) == 8 && longest > 10) continue;
-        // In double where that fits; 8 rows for longer paths only, whose registers hold
-        // a CU to 16 waves whatever the tile (784 features, paths of up to 16, 3000 rows:
-        // 0.55 against 0.78 ms in float), and 16 waves in float before 12 or 8 in double
-        // (700 rows of 60 trees, M = 1800: 16 waves 0.18 ms, 8 0.35).
-        const bool d = kWide && (RW == 16 || (RW == 8 && w > 8 && !is_short)) &&
-                       (int64_t)need(RW, w, false, true) <= whole;
-        const int64_t n = need(RW, w, false, d);
+        if (RW == 0 || (w == 16 && !kWide && longest > 10)) continue;
+        const int64_t n = need(RW, w, false, false);
         if (n > whole) continue;
-        const int groups = kWide || is_short ? cap / w : 1;
+        const int groups = !is_short ? 1 : (kWide ? 24 : 16) / w;
         const int per_cu = w * (int)std::min<int64_t>(groups, dev.lds_per_cu / n);
         if (per_cu > best) {
           best = per_cu;
           waves = w;
-          wide = d;
         }
       }
     }

@@ -40,12 +40,16 @@ constexpr int kQLong = 64;
 constexpr bool has_shape(bool f64, bool inter, int qmax, int rw, int waves, bool wide) {
   if (inter) return !wide && (waves == 8 || (waves == 16 && rw <= 16));
   const bool longer = qmax > kQShort;
-  if (f64 && rw <= 16) return !wide && (waves < 16 || qmax <= kQMid);
-  if (f64) return !wide && waves == 8;
+  if (f64) {
+    if (wide) return false;
+    if (rw > 16) return waves == 8;
+    if (waves == 16) return qmax <= kQMid;
+    return rw < 16 || (waves == 12 && longer);
+  }
   if (rw == 64) return wide && (waves == 8 || (waves == 12 && !longer) || (waves == 16 && qmax <= kQExt));
   if (rw == 32) return wide && (waves == 8 || (waves == 16 && longer && qmax <= kQExt));
-  if (rw == 16) return wide && (longer || waves == 12);
-  if (rw == 8) return !wide || waves == (longer ? 16 : 12);
+  if (rw == 16) return wide && waves == (longer ? 16 : 12);
+  if (rw == 8) return !wide || waves == 12 || (waves == 16 && longer);
   return !wide;
 }
 

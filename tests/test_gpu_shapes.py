@@ -21,15 +21,18 @@ SHAPES = [
     # 16 rows: the same, beyond 12 features
     (333, "f32", 13, 16, 16), (334, "f32", 13, 16, 16), (373, "f32", 20, 16, 16),
     (334, "f32", 12, 8, 16), (374, "f32", 13, 8, 16),
-    # 8 rows: 16 waves in double, then in float
-    (1337, "f32", 11, 8, 16), (1338, "f32", 11, 8, 16), (1430, "f32", 16, 8, 16),
+    # 8 rows: 16 and 12 waves in double, then in float
+    (1337, "f32", 11, 8, 16), (1338, "f32", 11, 8, 12), (1429, "f32", 16, 8, 12),
+    (1430, "f32", 16, 8, 16),
     (2007, "f32", 20, 8, 16), (2008, "f32", 11, 8, 12),
     # short paths: 12 waves twice a CU, on 16 and 8 rows in double, then in float
     (167, "f32", 8, 16, 12), (287, "f32", 8, 16, 12), (288, "f32", 8, 8, 12),
     (373, "f32", 8, 8, 12), (576, "f32", 8, 8, 12), (577, "f32", 8, 8, 12),
+    (1000, "f32", 8, 8, 16), (1100, "f32", 8, 8, 16),
     # fp64: 8 waves on 64 and 32 rows
     (40, "f64", 8, 64, 8), (68, "f64", 8, 64, 8), (69, "f64", 8, 32, 8), (81, "f64", 9, 64, 8),
     (82, "f64", 9, 32, 8), (142, "f64", 12, 32, 8),
+    (160, "f64", 8, 16, 16), (300, "f64", 8, 8, 16), (635, "f64", 8, 8, 16),
     # fp64: 16 waves to 10 features, then 12, whose registers hold a path
     (160, "f64", 9, 16, 16), (300, "f64", 10, 8, 16), (160, "f64", 11, 16, 12),
     (285, "f64", 12, 16, 12), (300, "f64", 12, 8, 12),

@@ -39,12 +39,15 @@ def planned(dtype, inter, qmax):
         return out | of(64, [8]) | of(32, [8]) | of(16, [8, 16]) | of(8, [8, 16]) | of(4, [8, 16])
     if dtype == "d":
         low = [8, 12, 16] if qmax <= 12 else [8, 12]
-        out |= of(16, low) | of(8, low) | of(4, low)
-        return out | of(64, [8]) | of(32, [8])
-    out |= of(8, [8, 12, 16]) | of(4, [8, 12, 16]) | of(16, [12] if qmax == 8 else [8, 12, 16], True)
-    out |= of(64, {8: [8, 12, 16], 64: [8]}.get(qmax, [8, 16]), True)
-    out |= of(32, {8: [8], 64: [8]}.get(qmax, [8, 16]), True)
-    return out | of(8, [12] if qmax == 8 else [16], True)
+        out |= of(8, low) | of(4, low) | of(64, [8]) | of(32, [8])
+        return out | of(16, {8: [16], 12: [12, 16]}.get(qmax, [12]))
+    out |= of(8, [8, 12, 16]) | of(4, [8, 12, 16])
+    if qmax == 8:
+        return (out | of(64, [8, 12, 16], True) | of(32, [8], True) | of(16, [12], True) |
+                of(8, [12], True))
+    out |= of(16, [16], True) | of(8, [12, 16], True)
+    tall = [8] if qmax == 64 else [8, 16]
+    return out | of(64, tall, True) | of(32, tall, True)
 
 
 def test_every_variant_is_built():
