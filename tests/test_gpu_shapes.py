@@ -55,3 +55,23 @@ def test_shape(orc, M, dtype, q, rows, waves):
     assert (cfg["rows_per_tile"], cfg["waves"], cfg["private_tiles"]) == (rows, waves, 0)
     got = gts.shap(model, torch.from_numpy(X).cuda()).cpu().numpy().astype(np.float64)
     assert_parity(got, orc.treeshap(ens, X), dtype, what=f"M={M} {dtype} {q} features")
+
+
+# (trees, depth, groups, rows): more bins than a workgroup's 4 waves in a group
+FEW = [(4, 5, 1, 13), (10, 7, 10, 9), (16, 7, 10, 47)]
+
+
+@pytest.mark.parametrize("trees,depth,groups,rows", FEW)
+def test_no_wave_takes_two_of_few_bins(orc, trees, depth, groups, rows):
+    """Slices enough that no wave has a second bin, also in a group of twice the mean."""
+    import torch
+    w = synth.random_workload(trees, num_trees=trees, max_depth=depth, p_split=0.85, M=20,
+                              num_groups=groups, n_bg=200, rows=rows)
+    model = gts.prepare(w.ensemble, "f32")
+    cfg = gts.launch_config(model, rows)
+    mean = model.desc.num_bins / groups
+    print("few bins", trees, groups, model.desc.num_bins, cfg, flush=True)
+    assert cfg["private_tiles"] == 1 and cfg["waves"] == 4 and mean > 4
+    assert cfg["slices"] * 4 >= (mean if groups == 1 else 2 * int(mean))
+    got = gts.shap(model, torch.from_numpy(w.X).cuda()).cpu().numpy().astype(np.float64)
+    assert_parity(got, orc.treeshap(w.ensemble, w.X), "f32", what=f"{trees} trees")
