@@ -288,11 +288,7 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
     }
     min_splits = std::min(min_splits, splits);
   }
-  // The rank tables cost a workgroup about 0.7 us a feature and serve only models
-  // with zero fractions: they come with work enough to pay for them (1000 rows of
-  // 100 trees of depth 8 over 14 features, one or two bins a wave: 68.8 us with
-  // them, 32.6 without).  Without them the per-path test finds the dead paths.
-  if (rank_off != 0 && bins_per_group < (int64_t)kRankMinBins * splits * waves) {
+  if (rank_off != 0 && !ranks_pay(M, bins_per_group, (int64_t)splits * waves)) {
     rank_off = 0;
     lds = need(RW, waves, priv, wide);
   }

@@ -157,10 +157,11 @@ def test_special_models(torch, orc):
 @pytest.mark.parametrize("M", [16, 17])
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 def test_rank_table_feature_limit(torch, orc, M, dtype):
-    """One-path-per-wave launches with private tiles test a whole bin for
-    dead (row, path) pairs from rank tables of the row tile when M <= 16, and
-    path by path above: 16 and 17 features, zero-cover splits and rows tied
-    on four values, 150 rows (three 64-row tiles, the last ragged)."""
+    """One-path-per-wave launches with private tiles test each path for dead
+    (row, path) pairs on a batch this small (test_gpu_rank_tables.py has the
+    test by rank tables, which serves M <= 16): 16 and 17 features, zero-cover
+    splits and rows tied on four values, 150 rows (three 64-row tiles, the last
+    ragged)."""
     w = synth.random_workload(60 + M, num_trees=14, max_depth=7, M=M, n_bg=30, rows=150)
     model = gts.prepare(w.ensemble, dtype)
     cfg = gts.launch_config(model, 150)
@@ -189,10 +190,8 @@ def spine_tree(feats, rng, zero_right):
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 def test_sixteen_feature_paths(torch, orc, dtype):
     """Paths of 12 to 16 features on a 16-feature model: the variant
-    unrolled for at most 16 features (fp64 arithmetic), and in fp32 the
-    one-path-per-wave launch whose rank tables cover 16 features and whose
-    scan over a path's zero-fraction elements spans up to 16 lanes; 150 rows
-    (three 64-row tiles, the last ragged)."""
+    unrolled for at most 16 features, and in fp32 the one-path-per-wave launch
+    with private tiles; 150 rows (three 64-row tiles, the last ragged)."""
     rng = np.random.default_rng(16)
     M = 16
     trees = []
@@ -215,8 +214,8 @@ def test_sixteen_feature_paths(torch, orc, dtype):
 def test_bins_without_live_paths(torch, orc):
     """Trees whose right subtree has zero cover: its paths carry two
     zero-fraction elements, and rows with x0 < 0.5 reach none of them, so
-    whole bins of these (longer) paths are dead for whole tiles and are not
-    staged; the left paths (cover 10 of 10) stay live.  Rows with x0 >= 0.5 in
+    all of these (longer) paths of whole bins are dead for whole tiles; the left
+    paths (cover 10 of 10) stay live.  Rows with x0 >= 0.5 in
     a later tile make some of them live there."""
     rng = np.random.default_rng(7)
     trees = []
