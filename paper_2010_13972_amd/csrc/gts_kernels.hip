@@ -265,16 +265,16 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
       // 4 bins a wave, one round of workgroups, of at least 4 bins each (100 trees
       // of depth 8 over 54 features: 1 row 128 slices 13.8 us, 1024 34.7; 200 rows
       // 128 18.7, 256 28.2; 1000 rows 32 32.8, 64 37.2), unless a wave then has two, which
-      // takes twice as long (13 rows, 6 bins for 4 waves: 1 slice 16.8 us, 6 12.4).  Of
-      // several groups some have more than the mean: for twice as many, while that leaves
-      // CUs without a workgroup (9 rows, 10 groups of 21 bins: 8 slices 15.5, 12 11.3; 300
-      // rows, 10 groups of 78 bins: 20 17.7, 32 26.9).  Fewer bins than waves are best in
+      // takes twice as long (13 rows, 6 bins for 4 waves: 1 slice 16.8 us, 6 12.4), as long
+      // as that leaves no CU with two workgroups (fp64, 10 000 rows, 5 bins: 1 slice 15.1, 5
+      // 19.5).  Of several groups some have more than the mean: for twice as many (9 rows,
+      // 10 groups of 21 bins: 8 slices 15.5, 12 11.3).  Fewer bins than waves are best in
       // one slice, which needs no clearing of phi: 9.3 and 12.2.
       if (bins_per_group < 4 * want * waves) {
         int64_t single = 1;
-        if (G == 1) single = (bins_per_group + waves - 1) / waves;
-        else if (bins_per_group >= waves)
-          single = std::min((2 * bins_per_group + waves - 1) / waves, dev.cus / base);
+        if (G == 1 || bins_per_group >= waves)
+          single = ((G == 1 ? 1 : 2) * bins_per_group + waves - 1) / waves;
+        single = std::min(single, dev.cus / base);
         want = std::min(std::max<int64_t>(1, target / 2 / base),
                         std::max<int64_t>({1, single, bins_per_group / 4}));
       }
