@@ -348,7 +348,7 @@ __global__ __launch_bounds__(64 * WAVES) void inter_quad_kernel(DevModel<T> d,
   for (int bi = gb0 + s + wave * L.splits; bi < gb1; bi += WAVES * L.splits) {
     const Bin<T> bin = load_bin(d, bi, lane);
     const BinIndex ix = index_bin(bin, lane);
-    stage_bin(&st->bin, bin, lane, ix);
+    stage_bin<false>(&st->bin, bin, lane, ix);
     for (uint64_t rest = ix.roots; rest != 0; rest &= rest - 1ull) {
       const int rl = __builtin_ctzll(rest);
       const int q = __builtin_amdgcn_readlane(ix.info, rl) & 0xff;

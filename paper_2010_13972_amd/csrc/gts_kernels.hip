@@ -171,7 +171,7 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
     // against 2842, of 11 2034 against 1973).  64 and 32 rows not for paths beyond 16
     // features, whose loops are faster on fewer: M = 95, 3000 rows, 64 rows 4.75 ms, 32
     // 3.91 (M = 350, 16 rows 4.7, 8 8.9).
-    const bool unrolled = longest <= kMaxUnrolledShapF64;
+    const bool unrolled = longest <= kMaxUnrolledExt;
     if (kWide && unrolled && (int64_t)need(64, 8, false, false) <= kSmallTile)
       take(64, 16, true, whole);
     take(32, 8, kWide, kHalfCu);
@@ -308,7 +308,7 @@ gts_status plan_launch(const gts_model* m, int64_t rows, const DeviceInfo& dev, 
   // the kernel variant: the model's longest path, in features
   plan.qmax = longest <= kQShort ? kQShort
               : (!INTER && longest <= kMaxUnrolledShap) ? kQMid
-              : (!INTER && longest <= kMaxUnrolledShapF64) ? kQExt
+              : (!INTER && longest <= kMaxUnrolledExt) ? kQExt
                                                            : kQLong;
   return GTS_OK;
 }

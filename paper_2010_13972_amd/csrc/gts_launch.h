@@ -20,7 +20,7 @@ constexpr int kMaxUnrolledShap = 12;
 constexpr int kMaxUnrolledInter = 8;
 // SHAP paths of 13-16 features run unrolled code in a variant of their own, since
 // they need more registers.
-constexpr int kMaxUnrolledShapF64 = 16;
+constexpr int kMaxUnrolledExt = 16;
 
 // Interaction values of paths of up to 16 features run by quadrature where the
 // model has longer ones than the unrolled code takes.

@@ -54,10 +54,11 @@
 // values a tile of doubles, which gfx950 adds to natively; for interaction values
 // an atomic add built from compare-and-swap, those of a path issued together so
 // their LDS round trips overlap; or, when a wave has a tile of its own and one
-// path at a time, a plain read-modify-write.  An
-// interaction pair is added to one of its two entries and the tile write sums
-// the mirror entries, so the output is exactly symmetric.  The tile is written
-// to HBM once (atomically added when several workgroups share the row tile).
+// path at a time, a plain read-modify-write.  An interaction pair is added to one
+// entry and the tile write gives both mirror entries that entry, so the output of
+// up to two slices is exactly symmetric (the sums of three and more may be rounded
+// in different orders).  The tile is written to HBM once (atomically added when
+// several workgroups share the row tile).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -187,19 +188,6 @@ __device__ __forceinline__ void lds_add(double* p, double v) {
   __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Bit patterns of the tile entries, for compare-and-swap.
-template <typename T> struct Bits;
-template <> struct Bits<float> {
-  using U = unsigned;
-  static __device__ __forceinline__ U of(float x) { return __float_as_uint(x); }
-  static __device__ __forceinline__ float val(U u) { return __uint_as_float(u); }
-};
-template <> struct Bits<double> {
-  using U = unsigned long long;
-  static __device__ __forceinline__ U of(double x) { return (U)__double_as_longlong(x); }
-  static __device__ __forceinline__ double val(U u) { return __longlong_as_double((long long)u); }
-};
-
 // The type of the phi tile's entries: double, whatever the model's type, in the wide
 // launches (shared tiles of SHAP values, where the planner finds room), else the
 // model's type.
@@ -238,25 +226,25 @@ __device__ __forceinline__ void tile_add(T* const (&p)[N], const V (&val)[N], co
     for (int i = 0; i < N; ++i)
       if (on[i]) lds_add(p[i], (T)val[i]);
   } else {
-    using U = typename Bits<T>::U;
-    U old[N], got[N];
+    // on the bit patterns
+    unsigned old[N], got[N];
     if constexpr (MODE == kBatched) {
 #pragma unroll
-      for (int i = 0; i < N; ++i) old[i] = *reinterpret_cast<const U*>(p[i]);
+      for (int i = 0; i < N; ++i) old[i] = *reinterpret_cast<const unsigned*>(p[i]);
 #pragma unroll
       for (int i = 0; i < N; ++i)
-        got[i] = on[i] ? atomicCAS(reinterpret_cast<U*>(p[i]), old[i],
-                                   Bits<T>::of(Bits<T>::val(old[i]) + val[i]))
+        got[i] = on[i] ? atomicCAS(reinterpret_cast<unsigned*>(p[i]), old[i],
+                                   __float_as_uint(__uint_as_float(old[i]) + (T)val[i]))
                        : old[i];
     } else {
       // every lane swaps, so no lane branches around its swap: an entry that
       // is off adds -0.0, which leaves every value as it is (-0.0 included)
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        const T add = on[i] ? val[i] : T(-0.0);
-        old[i] = *reinterpret_cast<const U*>(p[i]);
-        got[i] = atomicCAS(reinterpret_cast<U*>(p[i]), old[i],
-                           Bits<T>::of(Bits<T>::val(old[i]) + add));
+        const T add = on[i] ? (T)val[i] : T(-0.0);
+        old[i] = *reinterpret_cast<const unsigned*>(p[i]);
+        got[i] = atomicCAS(reinterpret_cast<unsigned*>(p[i]), old[i],
+                           __float_as_uint(__uint_as_float(old[i]) + add));
       }
     }
     bool retry = false;
@@ -390,7 +378,8 @@ __device__ __forceinline__ BinIndex index_bin(const Bin<T>& b, int lane) {
 
 // Stages a bin (indexed by index_bin); returns its number of paths.  On a
 // root lane, info holds the path's features | its zero-fraction elements << 8.
-template <typename T, bool GAPPED>
+// WEIGHTS: with v (1 - z) on the other elements (the unrolled interaction code).
+template <bool WEIGHTS, typename T, bool GAPPED>
 __device__ __forceinline__ int stage_bin(Stage<T, GAPPED>* st, const Bin<T>& b, int lane,
                                          const BinIndex& ix) {
   int slot = lane;
@@ -398,8 +387,11 @@ __device__ __forceinline__ int stage_bin(Stage<T, GAPPED>* st, const Bin<T>& b, 
     const uint64_t evens = __ballot(ix.root && (ix.len & 1) == 0);
     slot += __popcll(evens & ((1ull << ix.rl) - 1ull));
   }
-  const T v = __shfl(b.z, ix.rl);   // a root's zero-fraction slot holds v
-  const T w = ix.root ? v : v * (T(1) - b.z);
+  T w = b.z;   // a root's zero-fraction slot holds v
+  if constexpr (WEIGHTS) {
+    const T v = __shfl(b.z, ix.rl);
+    if (!ix.root) w = v * (T(1) - b.z);
+  }
   st->head[slot] = make_int4(b.feat, b.klo, (int)b.span,
                              sizeof(T) == 4 ? __float_as_int((float)b.z) : 0);
   typename Stage<T, GAPPED>::AuxT ax{};
@@ -778,7 +770,7 @@ __device__ __forceinline__ void path_fixed(const Stage<T, GAPPED>* st, int s, in
 template <typename T, typename A, bool UNIFORM, bool INTER, AddMode MODE, bool GAPPED, int QMAX>
 __device__ __forceinline__ void dispatch(int Q, const Stage<T, GAPPED>* st, int s, int q,
                                          const int* xrow, A* prow, int stride) {
-  static_assert(kMaxUnrolledShap == 12 && kMaxUnrolledShapF64 == 16 && kMaxUnrolledInter == 8,
+  static_assert(kMaxUnrolledShap == 12 && kMaxUnrolledExt == 16 && kMaxUnrolledInter == 8,
                 "update the case lists");
   static_assert(QMAX == kQShort || QMAX == kQMid || QMAX == kQExt || QMAX == kQLong,
                 "unknown variant");
@@ -967,7 +959,7 @@ __device__ __forceinline__ void process_bin(Stage<T, RW < 64>* st, const Bin<T>&
       rest = live_roots<T, QMAX>(b, lane, roots, info, rt);
       if (rest == 0) return;
     }
-    stage_bin(st, b, lane, ix);
+    stage_bin<INTER>(st, b, lane, ix);
     while (rest != 0) {
       const int rl = __builtin_ctzll(rest);
       rest &= rest - 1ull;
@@ -981,7 +973,7 @@ __device__ __forceinline__ void process_bin(Stage<T, RW < 64>* st, const Bin<T>&
   } else {
     constexpr int P = 64 / RW;
     const int j = lane / RW;
-    const int npaths = stage_bin(st, b, lane, ix);
+    const int npaths = stage_bin<INTER>(st, b, lane, ix);
     for (int base = 0; base < npaths; base += P) {
       const int t = base + j;
       const bool valid = t < npaths;
@@ -1104,7 +1096,7 @@ __global__ __launch_bounds__(64 * WAVES) void shap_kernel(
 
   // write the tile: phi[row][g][.]; the bias goes to the last entry.  An
   // interaction entry (a, b) and its mirror (b, a) both get the triangle's
-  // entry, so the output is exactly symmetric.
+  // entry.
   const T bias = d.bias[g];
   const int W = L.width;
   for (int i = threadIdx.x; i < RW * W; i += kThreads) {
