@@ -62,7 +62,28 @@ def test_random_edge_case_ensembles_bitwise(torch, orc, seed):
     assert_same(torch, orc, w.ensemble, f"random{seed}")
 
 
-def test_special_trees_bitwise(torch, orc):
+def full_tree(nodes, M):
+    """A full tree of the largest 2^k - 1 <= nodes nodes, then leaves split one by one."""
+    inner = (1 << ((nodes + 1).bit_length() - 2)) - 1
+    res = [(2 * n + 1, 2 * n + 2, n % M, 0.5, 1024.0, 0.0) for n in range(inner)]
+    res += [(-1, -1, -1, 0.0, 1.0, 0.25 * (n % 9)) for n in range(inner + 1)]
+    n = len(res) - 1
+    while len(res) < nodes:
+        res[n] = (len(res), len(res) + 1, n % M, 0.5, 1.0, 0.0)
+        res += [(-1, -1, -1, 0.0, 1.0, -1.0), (-1, -1, -1, 0.0, 0.0, 2.0)]
+        n -= 1
+    assert len(res) == nodes
+    return res
+
+
+# One workgroup a tree where all have at most 4096 nodes; a larger one anywhere sends the
+# ensemble through the kernels of a thread a node.  The larger tree comes first, so a
+# fault of another tree is not node 0's of tree 0.
+BOTH = pytest.mark.parametrize("larger", [[], [4097]], ids=["tree", "node"])
+
+
+@BOTH
+def test_special_trees_bitwise(torch, orc, larger):
     rng = np.random.default_rng(4)
     leaf = [(-1, -1, -1, 0.0, 10.0, 2.5)]
     stump = [(1, 2, 1, 0.5, 10.0, 0.0), (-1, -1, -1, 0, 3.0, -1.0), (-1, -1, -1, 0, 7.0, 4.0)]
@@ -73,12 +94,29 @@ def test_special_trees_bitwise(torch, orc):
     shuffled = [(2, 1, 0, 0.5, 10.0, 0.0), (-1, -1, -1, 0, 6.0, 1.5), (-1, -1, -1, 0, 4.0, -0.5),
                 (-1, -1, -1, 0, 1.0, 9.0)]
     trees = [leaf, stump, dup, chain_tree(63, 63, rng), shuffled, leaf]
+    trees += [full_tree(n, 7) for n in larger]
     ens = synth.ensemble_from_lists(trees, M=63, num_groups=2)
     say("device extraction special trees")
     assert_same(torch, orc, ens, "special trees")
 
 
-def test_errors_match_the_host(torch):
+@BOTH
+def test_cycle_apart_from_the_tree(torch, larger):
+    """Two nodes that are each other's child, with leaves, which no path from the root
+    reaches: not part of the tree, as on the host (the oracle takes no such input)."""
+    tree = [(1, 2, 1, 0.5, 10.0, 0.0), (-1, -1, -1, 0, 3.0, -1.0), (-1, -1, -1, 0, 7.0, 4.0),
+            (4, 5, 2, 0.5, 4.0, 0.0), (3, 6, 3, 0.5, 4.0, 0.0),
+            (-1, -1, -1, 0, 1.0, 3.0), (-1, -1, -1, 0, 1.0, 7.0)]
+    ens = synth.ensemble_from_lists([full_tree(n, 5) for n in larger] + [tree], M=5)
+    say("device extraction cycle", larger)
+    el, paths, bias = gts.extract_paths(ens)
+    d_el, d_paths, d_bias = device_extract(torch, ens)
+    assert d_paths == paths and d_el.tobytes() == el.tobytes()
+    assert d_bias.tobytes() == bias.tobytes()
+
+
+@BOTH
+def test_errors_match_the_host(torch, larger):
     good = [(1, 2, 0, 0.5, 10.0, 0.0), (-1, -1, -1, 0, 4.0, 1.0), (-1, -1, -1, 0, 6.0, 2.0)]
     cases = {
         "child out of range": [(1, 5, 0, 0.5, 10.0, 0.0)] + good[1:],
@@ -88,10 +126,11 @@ def test_errors_match_the_host(torch):
         "shared child": [(1, 1, 0, 0.5, 10.0, 0.0)] + good[1:],
         "cycle to the root": [(1, 2, 0, 0.5, 10.0, 0.0), (0, 2, 1, 0.5, 4.0, 0.0),
                               (-1, -1, -1, 0, 6.0, 2.0)],
+        "leaf value": [good[0], (-1, -1, -1, 0, 4.0, float("inf")), good[2]],
     }
     for what, tree in cases.items():
-        ens = synth.ensemble_from_lists([good, tree], M=2)
-        say("device extraction error", what)
+        ens = synth.ensemble_from_lists([full_tree(n, 2) for n in larger] + [good, tree], M=2)
+        say("device extraction error", what, larger)
         with pytest.raises(gts.GtsError) as host:
             gts.extract_paths(ens)
         with pytest.raises(gts.GtsError) as dev:
@@ -113,11 +152,13 @@ def doubled_chain(depth, below):
     return res
 
 
-def test_ranks_of_a_malformed_tree_are_not_used(torch):
+@BOTH
+def test_ranks_of_a_malformed_tree_are_not_used(torch, larger):
     """The ranks of such a tree would index far past the workspace: the call
     reports the error as the host does, and a buffer allocated behind the
     workspace keeps its bytes."""
-    ens = synth.ensemble_from_lists([doubled_chain(200, 8)], M=2)
+    ens = synth.ensemble_from_lists([full_tree(n, 2) for n in larger] + [doubled_chain(200, 8)],
+                                    M=2)
     dens = gts.DeviceEnsemble(ens)
     size = ctypes.c_int64(0)
     assert gts.lib().gts_extract_workspace_bytes(ens.num_trees, ens.num_nodes,
@@ -133,13 +174,40 @@ def test_ranks_of_a_malformed_tree_are_not_used(torch):
     assert bool((both[need:] == 0x5a).all())
 
 
-def test_too_long_merged_path(torch):
+@BOTH
+def test_too_long_merged_path(torch, larger):
     """64 distinct features on one path cannot fill a 64-lane bin."""
     rng = np.random.default_rng(1)
-    ens = synth.ensemble_from_lists([chain_tree(64, 64, rng)], M=64)
+    ens = synth.ensemble_from_lists([full_tree(n, 64) for n in larger] + [chain_tree(64, 64, rng)],
+                                    M=64)
     with pytest.raises(gts.GtsError) as dev:
         device_extract(torch, ens)
     assert dev.value.status == gts.GTS_EPATHLEN
+
+
+@BOTH
+@pytest.mark.parametrize("splits", [256, 257])
+def test_deepest_path(torch, orc, splits, larger):
+    """256 splits on a path are taken, on 5 features; 257 are refused."""
+    rng = np.random.default_rng(splits)
+    ens = synth.ensemble_from_lists([full_tree(n, 5) for n in larger] + [chain_tree(splits, 5, rng)],
+                                    M=5)
+    say("device extraction deep", splits, larger)
+    if splits == 256:
+        assert_same(torch, orc, ens, "256 splits")
+        return
+    with pytest.raises(gts.GtsError) as dev:
+        device_extract(torch, ens)
+    assert dev.value.status == gts.GTS_EINVAL
+    assert "256" in str(dev.value)
+
+
+@pytest.mark.parametrize("M", [5, 90])
+@pytest.mark.parametrize("nodes", [4095, 4097])
+def test_trees_at_one_workgroups_limit(torch, orc, M, nodes):
+    trees = [full_tree(n, M) for n in (1, 3, nodes, 7)]
+    say("device extraction nodes", nodes, M)
+    assert_same(torch, orc, synth.ensemble_from_lists(trees, M=M), f"{nodes} nodes")
 
 
 @pytest.mark.parametrize("M", [5, 90])
